@@ -338,7 +338,7 @@ size_t eb_qlinear_stack_workspace_bytes(const eb_qlinear_op *ops, int32_t n_ops)
  *   that an earlier op of the run writes (decided by address ranges of x, y,
  *   the weights, norm_weight and residual) is executed by fewer launches: m == 1
  *   ops with the same formats by one persistent GEMV launch per K size class,
- *   small-m MFMA ops (m <= 128) by one persistent launch, larger-m MFMA ops
+ *   small-m MFMA ops (m <= 128) by one launch over their tiles, larger-m MFMA ops
  *   with the same formats by one grouped launch over all their output tiles
  *   (whose mostly-padded last row tiles may go to a small-m launch).  Results
  *   are those of running the ops in order; the m == 1 fusion is bitwise

@@ -156,9 +156,8 @@ eb_status check_op(const eb_qlinear_op &o, int32_t path) {
 // without a workspace, replayed from a graph; Q4_0 and Q8_0 at the decode /
 // prefill / action-expert shapes): the GEMV wins at m = 1 everywhere; at
 // m = 2..4 when the matrix has 4096 rows or more (with 1024 or 2048 the
-// matrix cores win by 20-55%); at m = 5..8 where, in addition, the narrow
-// matrix-core kernel does not apply (k > 2048: the unsplit tile kernel loses
-// by 5-30%; the narrow kernel wins by 15-50%, or ties within 2%).
+// matrix cores win by 20-55%); at m = 5..8 where, in addition, k > 2048 (up
+// to there the small-m matrix-core kernel wins by 15-50%).
 // Q6_S: its GEMV up to m = 4, its matrix-core kernel beyond.
 int32_t pick_path(int32_t type, int32_t xt, int64_t m, int64_t n, int64_t k) {
   (void)xt;
@@ -167,7 +166,7 @@ int32_t pick_path(int32_t type, int32_t xt, int64_t m, int64_t n, int64_t k) {
   if (m == 1) return EB_PATH_GEMV;
   if (n < 4096) return EB_PATH_MFMA;
   if (m <= 4) return EB_PATH_GEMV;
-  return narrow_fits(m, n, k, 1) ? EB_PATH_MFMA : EB_PATH_GEMV;
+  return k <= 2048 ? EB_PATH_MFMA : EB_PATH_GEMV;
 }
 
 // Bytes of normalised activations an op on the MFMA path needs (256-aligned).
@@ -329,20 +328,6 @@ struct NormJob {
 // have reserved == 0).
 constexpr int32_t kRelX = 1;
 
-// Cap on the workgroups of a split-off-rows launch running beside a grouped
-// launch (0: one per CU, as alone).  Measured on the m = 816 VLM prefill pass:
-// no cap 3.89 ms, 128 or 64 workgroups 3.91-3.93 ms, 32 4.17 ms, 16 7.47 ms,
-// the launch after the grouped one instead of beside it 4.00 ms.  Tuning hook:
-// EB_STACK_SIDE_GROUPS (read once).
-int side_groups() {
-  static const int g = [] {
-    const char *e = std::getenv("EB_STACK_SIDE_GROUPS");
-    const int v = e ? std::atoi(e) : 0;
-    return v >= 8 ? v : 0;
-  }();
-  return g;
-}
-
 struct Step {
   int op = -1;        // single op index, or -1 for a fused launch
   bool mfma = false;  // single op on the MFMA path, run with plan `mp`
@@ -353,16 +338,14 @@ struct Step {
   size_t table = 0;   // first entry in the device table (M1Op or MMOp)
   int nops = 0;
   int64_t units = 0, rows = 0;
-  int mm_cfg = 0, groups = 0;
-  size_t wg = 0;      // first entry of the workgroup ranges
+  int mm_cfg = 0;
+  RowsTiles rt;       // fused small-m launch
   bool gm = false;    // grouped MFMA launch (op == -1): table entries from `table`,
   size_t order = 0;   // workgroup entries from `order`
   int64_t entries = 0;
   std::vector<NormJob> norms;  // prologue row kernels run before the step
   bool side = false;  // fused launch of split-off rows that runs on the side stream,
                       // beside the grouped launch before it
-  bool hl = true;     // fused small-m launch: bfloat16 hi/lo weight pairs (not for the
-                      // split-off rows of large-m ops, whose bound is the large-m one)
   bool norm_next = false;   // single split MFMA op whose reduction also normalises
                             // its fp32 output for the next step's prologue
   bool pre_normed = false;  // single MFMA op whose prologue that reduction ran
@@ -372,7 +355,6 @@ struct Plan {
   std::vector<Step> steps;
   M1Op *table = nullptr;  // device copy of every fused GEMV launch's op table
   MMOp *mmtable = nullptr;  // same for fused MFMA launches
-  int64_t *mmwg = nullptr;  // their workgroup unit ranges
   GOp *gmtable = nullptr;   // grouped MFMA launches: op table
   int2 *gmorder = nullptr;  // and workgroup (op, tile) entries
   float *ws = nullptr;    // split-K workspace shared by the plan's MFMA steps (run in order)
@@ -395,8 +377,8 @@ bool fusable(const eb_qlinear_op &o) {
   return o.m == 1 && gemv_fits(1, o.w.k) && m1_fusable(o.w.type, o.m, o.w.k, o.epilogue);
 }
 
-// MFMA ops that may join a fused launch.  The fused kernel addresses tiles of
-// up to 256 rows with 31-bit offsets.  EB_STACK_FUSE_MAXM (default 128) caps
+// MFMA ops that may join a fused launch.  The fused kernel addresses tiles
+// with 31-bit offsets.  EB_STACK_FUSE_MAXM (default 128) caps
 // the rows of a fused op; small-m single launches are latency-bound, large-m
 // ones less so.
 int64_t mm_max_m() {
@@ -427,7 +409,6 @@ bool mm_fusable(const eb_qlinear_op &o) {
 eb_status build_plan(const eb_qlinear_op *ops, int32_t n_ops, uint8_t *wsbase, Plan &P) {
   std::vector<M1Op> host;
   std::vector<MMOp> mmhost;
-  std::vector<int64_t> mmwg;
   std::vector<GOp> gmhost;
   std::vector<int2> gmorder;
   const bool fuse = !env_off("EB_STACK_FUSE");
@@ -449,48 +430,29 @@ eb_status build_plan(const eb_qlinear_op *ops, int32_t n_ops, uint8_t *wsbase, P
     xoff += xhat_bytes(o);
     return c;
   };
-  // one fused small-m launch over `list` (same weight, x and y formats)
-  auto add_mm_step = [&](const std::vector<eb_qlinear_op> &list, int max_groups = 0,
-                         bool hl = true) {
-    int64_t max_m = 0;
-    for (const eb_qlinear_op &o : list) max_m = std::max(max_m, o.m);
+  // one fused small-m launch over `list` (same weight and x formats), longest
+  // k first, so that the last workgroups to start are short ones
+  auto add_mm_step = [&](std::vector<eb_qlinear_op> list) {
+    std::stable_sort(list.begin(), list.end(),
+                     [](const eb_qlinear_op &a, const eb_qlinear_op &b) { return a.w.k > b.w.k; });
     Step s;
     s.mm = true;
-    s.hl = hl;
     s.type = list[0].w.type;
     s.xt = list[0].x_type;
-    s.yt = list[0].y_type;
-    s.mm_cfg = mm_cfg(max_m);
     s.table = mmhost.size();
     std::vector<MMOp> run;
-    int64_t units = 0;
     for (const eb_qlinear_op &o : list) {
-      const Layout L = layout_of(o.w.type, o.w.n, o.w.k);
-      MMOp e{};
-      e.w = static_cast<const uint8_t *>(o.w.data);
-      e.x = static_cast<const uint16_t *>(o.x);
-      e.y = o.y;
-      e.d_off = L.d_off;
-      units += mm_tiles(s.mm_cfg, o.m, o.w.n);
-      e.unit_end = units;
-      e.ds = (int32_t)L.ds;
-      e.m = (int32_t)o.m;
-      e.n = (int32_t)o.w.n;
-      e.k = (int32_t)o.w.k;
-      e.tiles_n = (int32_t)mm_tiles(s.mm_cfg, 1, o.w.n);
-      e.nk = (int32_t)((o.w.k + mm_bk(s.mm_cfg) - 1) / mm_bk(s.mm_cfg));
-      e.yt = o.y_type;
-      e.pad = o.reserved == kRelX;  // x is an offset into the plan's buffer
-      e.f = fuse_of(o);
-      run.push_back(e);
+      run.push_back(rows_op(o.w.type, o.w.data, o.w.n, o.w.k, o.x, o.m, o.y, o.y_type, fuse_of(o)));
+      run.back().pad = o.reserved == kRelX;  // x is an offset into the plan's buffer
     }
-    std::vector<int64_t> wg;
-    s.groups = mm_partition(run, s.mm_cfg, wg, max_groups);
+    s.rt = rows_plan_multi(run, device_cu_count());
+    for (MMOp &e : run) {
+      s.units += rows_units(s.rt, e.m, e.n);
+      e.unit_end = s.units;
+      e.tiles_n = (e.n + 16 * s.rt.nt - 1) / (16 * s.rt.nt);
+    }
     s.nops = (int)run.size();
-    s.units = units;
-    s.wg = mmwg.size();
     mmhost.insert(mmhost.end(), run.begin(), run.end());
-    mmwg.insert(mmwg.end(), wg.begin(), wg.end());
     P.steps.push_back(s);
   };
   auto gops_of = [](const std::vector<eb_qlinear_op> &list) {
@@ -613,7 +575,7 @@ eb_status build_plan(const eb_qlinear_op *ops, int32_t n_ops, uint8_t *wsbase, P
             for (const eb_qlinear_op &t : tails)
               if ((t.y_type == EB_F32) == (wide == 1)) cls.push_back(t);
             if (cls.empty()) continue;
-            add_mm_step(cls, overlap ? side_groups() : 0, false);
+            add_mm_step(cls);
             P.steps.back().side = overlap;
           }
           i = j;
@@ -719,7 +681,6 @@ eb_status build_plan(const eb_qlinear_op *ops, int32_t n_ops, uint8_t *wsbase, P
   };
   const size_t t_m1 = take(host.size() * sizeof(M1Op));
   const size_t t_mm = take(mmhost.size() * sizeof(MMOp));
-  const size_t t_wg = take(mmwg.size() * sizeof(int64_t));
   const size_t t_gm = take(gmhost.size() * sizeof(GOp));
   const size_t t_go = take(gmorder.size() * sizeof(int2));
   const size_t t_tables = off;
@@ -730,7 +691,6 @@ eb_status build_plan(const eb_qlinear_op *ops, int32_t n_ops, uint8_t *wsbase, P
   P.wsbase = wsbase;
   P.table = host.empty() ? nullptr : reinterpret_cast<M1Op *>(wsbase + t_m1);
   P.mmtable = mmhost.empty() ? nullptr : reinterpret_cast<MMOp *>(wsbase + t_mm);
-  P.mmwg = mmwg.empty() ? nullptr : reinterpret_cast<int64_t *>(wsbase + t_wg);
   P.gmtable = gmhost.empty() ? nullptr : reinterpret_cast<GOp *>(wsbase + t_gm);
   P.gmorder = gmorder.empty() ? nullptr : reinterpret_cast<int2 *>(wsbase + t_go);
   P.ws = P.ws_bytes ? reinterpret_cast<float *>(wsbase + t_ws) : nullptr;
@@ -748,7 +708,6 @@ eb_status build_plan(const eb_qlinear_op *ops, int32_t n_ops, uint8_t *wsbase, P
     };
     put(t_m1, host.data(), host.size() * sizeof(M1Op));
     put(t_mm, mmhost.data(), mmhost.size() * sizeof(MMOp));
-    put(t_wg, mmwg.data(), mmwg.size() * sizeof(int64_t));
     put(t_gm, gmhost.data(), gmhost.size() * sizeof(GOp));
     put(t_go, gmorder.data(), gmorder.size() * sizeof(int2));
     if (hipMemcpy(wsbase, img.data(), t_tables, hipMemcpyHostToDevice) != hipSuccess)
@@ -795,8 +754,8 @@ eb_status run_plan(const eb_qlinear_op *ops, const Plan &P, hipStream_t s, hipSt
         return EB_ERR_HIP;
       for (size_t q = 1; q <= nside; ++q) {
         const Step &t = P.steps[i + q];
-        if (launch_mfma_multi(t.type, t.xt, t.hl, t.yt, t.mm_cfg, P.mmtable + t.table, t.nops,
-                              P.mmwg + t.wg, t.groups, side) != hipSuccess)
+        if (launch_rows_multi(t.type, t.xt, t.rt, P.mmtable + t.table, t.nops, t.units, side) !=
+            hipSuccess)
           return EB_ERR_HIP;
       }
       if (hipEventRecord(P.join, side) != hipSuccess) return EB_ERR_HIP;
@@ -807,8 +766,8 @@ eb_status run_plan(const eb_qlinear_op *ops, const Plan &P, hipStream_t s, hipSt
                               st.entries, s) != hipSuccess)
         return EB_ERR_HIP;
     } else if (st.mm) {
-      if (launch_mfma_multi(st.type, st.xt, st.hl, st.yt, st.mm_cfg, P.mmtable + st.table, st.nops,
-                            P.mmwg + st.wg, st.groups, s) != hipSuccess)
+      if (launch_rows_multi(st.type, st.xt, st.rt, P.mmtable + st.table, st.nops, st.units, s) !=
+          hipSuccess)
         return EB_ERR_HIP;
     } else if (st.mfma) {
       const eb_qlinear_op &o = ops[st.op];

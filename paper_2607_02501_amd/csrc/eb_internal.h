@@ -139,11 +139,17 @@ hipError_t launch_gemv_m1_multi(int32_t type, int32_t xt, int ns, const M1Op *de
 // MFMA path: any m.  A plan fixes the tile configuration and the split of K
 // over workgroups; with splits > 1 the launch needs ws_bytes of fp32 workspace
 // (partial sums, summed in order by a second kernel).
+struct RowsTiles {        // small-m kernel: 16 nt weight rows x 16 mb rows of x per workgroup
+  int nt = 0, mb = 0;
+  int splits = 1;         // of k
+  int64_t ws_stride = 0;  // floats between the partial outputs of two splits
+};
 struct MfmaPlan {
   int cfg = 0;
   bool q6 = false;        // Q6_S weights: the Q6_S kernel (any m, no split)
   bool hl = false;        // bfloat16 activations at m <= 128: hi/lo weight tiles
-  bool narrow = false;    // m <= kNarrowMaxM: the narrow kernel (splits > 1: plus the reduction)
+  bool rows = false;      // the small-m kernel with tiles `rt` (splits > 1: plus the reduction)
+  RowsTiles rt;
   int splits = 1;
   int kts = 0;            // K-tiles of 64 per split
   int64_t ws_stride = 0;  // floats between the partial outputs of two splits
@@ -170,19 +176,6 @@ template <int QT, int XT>
 hipError_t mfma_tile_launch(int cfg, bool hl, const void *wdata, int64_t n, int64_t k, const void *x,
                             int64_t m, void *y, int32_t yt, const Fuse &f, int sp, int kts,
                             float *ws, int64_t st, hipStream_t s);
-// Lone small-m projections (m <= kNarrowMaxM) in one launch: 16 weight rows
-// and the whole of k per workgroup, k split over its waves and the partial
-// tiles added through LDS (mfma_narrow.hip).  hl: bfloat16 hi/lo pairs.
-// When the 16-row workgroups do not fill the GPU, k is split (narrow_splits)
-// and each split writes fp32 partial sums for the ordered reduction.
-constexpr int64_t kNarrowMaxM = 64;
-constexpr int64_t kNarrowMaxK = 2048;  // k per split
-constexpr int kNarrowMaxSplits = 8;
-bool narrow_fits(int64_t m, int64_t n, int64_t k, int splits);
-int narrow_splits(int64_t n, int64_t k, int cus);
-hipError_t launch_mfma_narrow(int32_t type, const void *wdata, int64_t n, int64_t k, const void *x,
-                              int32_t xt, bool hl, int64_t m, void *y, int32_t yt, const Fuse &f,
-                              int splits, float *ws, int64_t ws_stride, hipStream_t s);
 // Q6_S weights, m <= 8 (gemv_q6.hip): a wave per pair of weight rows, lanes
 // over 32-weight chunks, fp32 products of the 6-bit codes and x staged in LDS.
 bool gemv_q6_fits(int64_t m, int64_t n, int64_t k);
@@ -239,40 +232,40 @@ template <int QT, int XT>
 hipError_t mfma_tile_launch_grouped(int cfg, const GOp *ops, const int2 *order, int64_t entries,
                                     hipStream_t s);
 
-// Fused MFMA launch over several independent ops of a stack: one persistent
-// launch whose workgroups each run a contiguous range of output tiles
-// (units), balanced by K-tile steps, as one continuous load/compute pipeline.
-// The table and the per-workgroup unit ranges live in device memory.
+// Small-m kernel (mfma_rows.h): lone projections and fused launches over
+// several independent ops of a stack, one workgroup per output tile.  The
+// table of a fused launch lives in device memory.
 struct MMOp {
   const uint8_t *w;    // planar weights
   const uint16_t *x;   // activations [m][k]
   void *y;             // outputs [m][n]
   int64_t d_off;       // scale-plane offset
-  int64_t unit_end;    // tiles of this op and all ops before it
+  int64_t unit_end;    // workgroups of this op and all ops before it
   int32_t ds, m, n, k; // ds: scale-plane row stride (elements)
-  int32_t tiles_n, nk, yt, pad;
+  int32_t tiles_n, yt, pad;
   Fuse f;
 };
 constexpr int64_t kMMaxK = int64_t(1) << 22;  // k < this keeps per-tile byte spans in 31 bits
-int mm_cfg(int64_t max_m);                // tile configuration for a run
-int64_t mm_tiles(int cfg, int64_t m, int64_t n);
-int mm_bk(int cfg);                       // k covered by one step of the configuration
-// The 128-wide-step fused kernel (configuration 0), in its own source file.
-hipError_t launch_lds2(int32_t type, int32_t xt, bool hl, int32_t yt, const MMOp *ops, int nops,
-                       const int64_t *wg, int groups, hipStream_t s);
-// Fills the unit ranges wg[0..groups] (balanced by steps) for a table whose
-// unit_end / nk are set; returns the number of workgroups to launch.
-// Workgroup unit ranges of a fused small-m launch; max_groups > 0 caps the
-// workgroup count (rounded to a multiple of 8).
-int mm_partition(const std::vector<MMOp> &ops, int cfg, std::vector<int64_t> &wg,
-                 int max_groups = 0);
-// All ops of one launch share the weight format, x type and y type.
-// groups must be a positive multiple of 8 (mm_partition's result).
-// hl: bfloat16 activations with w_hat as hi/lo pairs (ignored for binary16);
-// a launch of only the split-off rows of large-m ops runs without (the ops'
-// bound is the large-m one, w_hat rounded once).
-hipError_t launch_mfma_multi(int32_t type, int32_t xt, bool hl, int32_t yt, int cfg, const MMOp *dev_ops,
-                             int nops, const int64_t *dev_wg, int groups, hipStream_t s);
+constexpr int64_t kRowsMaxM = 128;
+constexpr int kRowsMaxSplits = 8;
+bool rows_fits(int64_t m, int64_t n, int64_t k);
+// Tile and split of k of a lone projection; partial sums take at most max_ws bytes.
+RowsTiles rows_plan(int64_t m, int64_t n, int64_t k, size_t max_ws, int cus);
+RowsTiles rows_plan_multi(const std::vector<MMOp> &ops, int cus);  // of a fused run
+int64_t rows_units(const RowsTiles &t, int64_t m, int64_t n);      // its workgroups for one op
+MMOp rows_op(int32_t type, const void *w, int64_t n, int64_t k, const void *x, int64_t m, void *y,
+             int32_t yt, const Fuse &f);
+hipError_t launch_rows(int32_t type, int32_t xt, const RowsTiles &t, const MMOp &o, float *ws,
+                       hipStream_t s);
+// All ops of one launch share the weight format and x type.
+hipError_t launch_rows_multi(int32_t type, int32_t xt, const RowsTiles &t, const MMOp *dev_ops,
+                             int nops, int64_t units, hipStream_t s);
+template <int QT>
+hipError_t rows_lone(int32_t xt, const RowsTiles &t, const MMOp &o, int splits, float *ws,
+                     int64_t ws_stride, hipStream_t s);
+template <int QT>
+hipError_t rows_multi(int32_t xt, const RowsTiles &t, const MMOp *ops, int nops, int64_t units,
+                      hipStream_t s);
 
 // number of compute units of the current device (cached per device)
 int device_cu_count();

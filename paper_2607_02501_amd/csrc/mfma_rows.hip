@@ -1,0 +1,121 @@
+// mfma_rows.hip -- host side of the small-m matrix-core path (m <= 128, Q8_0
+// and Q4_0; paper section 3.2, backend-specific dispatch): the choice of tile
+// and split of k for a lone projection, the tile of a fused run, and the
+// dispatch to the kernels (mfma_rows.h).
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+
+#include "eb_internal.h"
+
+namespace eb {
+
+namespace {
+
+constexpr int kStepBlocks = 8;  // blocks of k per step of a lone launch (its waves)
+
+// Estimated time (us) of a lone launch: a launch and its first copies, then
+// for every round of workgroups over the CUs its steps of k, each with a part
+// for the rows of x, for the weight rows and for their product.  Fitted to
+// launches of 1024..4096 -> 1024..8192 at 16, 50, 77 and 128 rows (Q8_0,
+// bfloat16): within 15%, and it ranks the tiles as the measurements do.
+double lone_us(int nt, int mb, int splits, int64_t m, int64_t n, int64_t k, int cus) {
+  const int64_t units = ((n + 16 * nt - 1) / (16 * nt)) * ((m + 16 * mb - 1) / (16 * mb)) * splits;
+  const int64_t steps = (k / kQK + kStepBlocks - 1) / kStepBlocks;
+  const double step = 0.05 + 0.08 * mb + 0.12 * nt + 0.031 * nt * mb;
+  double t = 3.0 + (double)((units + cus - 1) / cus) * (double)((steps + splits - 1) / splits) * step;
+  // the reduction of the partial sums: a launch, and their traffic
+  if (splits > 1) t += 3.2 + (double)(splits + 1) * (double)m * (double)n * 4 / 4e6;
+  return t;
+}
+
+}  // namespace
+
+bool rows_fits(int64_t m, int64_t n, int64_t k) {
+  // offsets inside a tile's rows of x, weights and y stay below 2^31 (an
+  // offset of 2^31 or more reads zero and stores nothing)
+  return m >= 1 && m <= kRowsMaxM && 64 * k * 2 < 0x7fff0000LL && 64 * n * 4 < 0x7fff0000LL;
+}
+
+RowsTiles rows_plan(int64_t m, int64_t n, int64_t k, size_t max_ws, int cus) {
+  // When the 16-row tiles of the weights leave two thirds of the CUs idle, k
+  // is split whatever the estimate says: in a layer chain the reduction then
+  // also normalises for the next projection, a launch that would follow anyway.
+  const int64_t wgs = (n + 15) / 16, steps = (k / kQK + kStepBlocks - 1) / kStepBlocks;
+  const int most = (int)std::max<int64_t>(1, std::min<int64_t>(kRowsMaxSplits, steps));
+  const bool split = cus / wgs >= 3 && most > 1;
+  RowsTiles best;
+  double best_t = 0;
+  for (int sp = 1; sp <= most; ++sp) {
+    const int64_t stride = (m * n + 63) / 64 * 64;
+    if (sp > 1 && (size_t)(stride * sp * 4) > max_ws) break;
+    if (sp > 1 && (steps + sp - 1) / sp == (steps + sp - 2) / (sp - 1)) continue;  // no shorter
+    for (int nt = 1; nt <= 4; nt *= 2)
+      for (int mb = 1; mb <= 4; ++mb) {
+        if (mb > 1 && 16 * (mb - 1) >= m) continue;
+        const double t = lone_us(nt, mb, sp, m, n, k, cus);
+        if (best.nt == 0 || (split && best.splits == 1 && sp > 1) || t < best_t) {
+          best_t = t;
+          best.nt = nt;
+          best.mb = mb;
+          best.splits = sp;
+          best.ws_stride = sp > 1 ? stride : 0;
+        }
+      }
+  }
+  return best;
+}
+
+int64_t rows_units(const RowsTiles &t, int64_t m, int64_t n) {
+  return round_up((n + 16 * t.nt - 1) / (16 * t.nt), 8) * ((m + 16 * t.mb - 1) / (16 * t.mb));
+}
+
+RowsTiles rows_plan_multi(const std::vector<MMOp> &ops, int cus) {
+  int max_m = 1;
+  for (const MMOp &o : ops) max_m = std::max(max_m, (int)o.m);
+  // the fewest row tiles of at most 64 rows, evenly high; the widest weight
+  // tile that still gives every CU a workgroup (wider ones read x less often)
+  RowsTiles t;
+  const int blocks = (max_m + 15) / 16, tiles_m = (blocks + 3) / 4;
+  t.mb = (blocks + tiles_m - 1) / tiles_m;
+  for (t.nt = 4; t.nt > 1; t.nt /= 2) {
+    int64_t units = 0;
+    for (const MMOp &o : ops) units += rows_units(t, o.m, o.n);
+    if (units >= cus) break;
+  }
+  return t;
+}
+
+hipError_t launch_rows(int32_t type, int32_t xt, const RowsTiles &t, const MMOp &o, float *ws,
+                       hipStream_t s) {
+  if (!rows_fits(o.m, o.n, o.k) || (t.splits > 1 && !ws)) return hipErrorInvalidValue;
+  float *part = t.splits > 1 ? ws : nullptr;
+  if (type == EB_Q4_0) return rows_lone<EB_Q4_0>(xt, t, o, t.splits, part, t.ws_stride, s);
+  return rows_lone<EB_Q8_0>(xt, t, o, t.splits, part, t.ws_stride, s);
+}
+
+hipError_t launch_rows_multi(int32_t type, int32_t xt, const RowsTiles &t, const MMOp *dev_ops,
+                             int nops, int64_t units, hipStream_t s) {
+  if (nops < 1 || units < 1 || units > 0x7fffffff) return hipErrorInvalidValue;
+  if (type == EB_Q4_0) return rows_multi<EB_Q4_0>(xt, t, dev_ops, nops, units, s);
+  return rows_multi<EB_Q8_0>(xt, t, dev_ops, nops, units, s);
+}
+
+MMOp rows_op(int32_t type, const void *w, int64_t n, int64_t k, const void *x, int64_t m, void *y,
+             int32_t yt, const Fuse &f) {
+  const Layout L = layout_of(type, n, k);
+  MMOp e{};
+  e.w = static_cast<const uint8_t *>(w);
+  e.x = static_cast<const uint16_t *>(x);
+  e.y = y;
+  e.d_off = L.d_off;
+  e.ds = (int32_t)L.ds;
+  e.m = (int32_t)m;
+  e.n = (int32_t)n;
+  e.k = (int32_t)k;
+  e.yt = yt;
+  e.f = f;
+  return e;
+}
+
+}  // namespace eb

@@ -9,11 +9,11 @@ _FILES = {
     # GEMV kernels (m <= 8)
     "gemv": ("gemv.hip", "gemv_common.h") + _COMMON,
     # tile kernel of the MFMA path (single ops, split-K, grouped launches)
-    "mfma": ("mfma.hip", "mfma_tile.h", "mfma_narrow.hip", "mfma_q8_0_bf16.hip", "mfma_q8_0_f16.hip",
+    "mfma": ("mfma.hip", "mfma_tile.h", "mfma_q8_0_bf16.hip", "mfma_q8_0_f16.hip",
              "mfma_q4_0_bf16.hip", "mfma_q4_0_f16.hip", "mfma_q6_s_bf16.hip", "mfma_q6_s_f16.hip",
              "mfma_common.h", "norm.hip") + _COMMON,
     # fused small-m MFMA kernels (m <= 128)
-    "mm": ("mfma_lds2.hip", "mfma_multi.hip", "mfma_common.h", "mm_common.h", "norm.hip") + _COMMON,
+    "mm": ("mfma_rows.h", "mfma_rows.hip", "mfma_rows_q8_0.hip", "mfma_rows_q4_0.hip", "mfma_common.h", "norm.hip") + _COMMON,
     # the Q6_S kernel (every m)
     "q6": ("mfma_q6.hip", "mfma_common.h", "norm.hip") + _COMMON,
     "gemv_q6": ("gemv_q6.hip", "gemv_common.h") + _COMMON,
@@ -31,8 +31,6 @@ def family(symbol: str) -> str:
         return "i8"
     if symbol.startswith("mm_q6"):
         return "q6"
-    if symbol.startswith("mm_narrow"):
-        return "mfma"
     if symbol.startswith("mm_"):
         return "mm"
     return "mfma"
