@@ -31,7 +31,7 @@ struct Layout {
   int64_t ss = 0;      // Q6_S: its row stride (bytes, k / 16)
 };
 
-inline Layout layout_of(int32_t type, int64_t n, int64_t k) {
+__host__ __device__ inline Layout layout_of(int32_t type, int64_t n, int64_t k) {
   Layout L;
   L.nb = k / kQK;
   L.qs_row = L.nb * qs_bytes_per_block(type);
@@ -49,7 +49,7 @@ inline Layout layout_of(int32_t type, int64_t n, int64_t k) {
 }
 
 // weights per canonical block and bytes per canonical block
-inline int64_t block_elems(int32_t type) { return type == EB_Q6_S ? kQK6 : kQK; }
+__host__ __device__ inline int64_t block_elems(int32_t type) { return type == EB_Q6_S ? kQK6 : kQK; }
 inline int64_t canonical_block_bytes(int32_t type) {
   return type == EB_Q6_S ? 2 + 16 + 192 : 2 + qs_bytes_per_block(type);
 }
