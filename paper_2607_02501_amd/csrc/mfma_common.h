@@ -249,6 +249,40 @@ __device__ inline void wait_vm_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// LDS rows of CPR 16-byte chunks: chunk c of row r is stored at position
+// c ^ chunk_swz<CPR>(r), so that 16 consecutive rows read at one chunk index
+// fall on 16 different 16-byte bank groups.
+template <int CPR>
+__device__ inline uint32_t chunk_swz(uint32_t r) {
+  if constexpr (CPR >= 16) return r & 15;
+  return (r / (16 / CPR)) & (CPR - 1);
+}
+
+typedef int i32x4_t __attribute__((ext_vector_type(4)));
+
+// Raw buffer descriptor as four words (rsrc), for the copies below.
+__device__ inline i32x4_t rsrc4(const void *base, uint32_t bytes) {
+  const uint64_t a = reinterpret_cast<uint64_t>(base);
+  return i32x4_t{(int)(uint32_t)a, (int)(uint32_t)(a >> 32) & 0xffff, (int)bytes, 0x00020000};
+}
+
+// The descriptor of the same buffer from `by` bytes further on.
+__device__ inline void advance(i32x4_t &r, uint32_t by) {
+  const uint64_t a = ((uint64_t)(uint32_t)r[1] << 32 | (uint32_t)r[0]) + by;
+  r[0] = (int)(uint32_t)a;
+  r[1] = (int)(uint32_t)(a >> 32);
+  r[2] -= (int)by;
+}
+
+// Copies 16 bytes per lane (lane l from offset voff of r) to LDS bytes
+// lds + 16 l; offsets past the descriptor copy zeros.  Written out because
+// the compiler makes every LDS read wait for such copies it knows of, the
+// ones into other stages too; the step's own wait and barrier order them.
+__device__ inline void copy_lds(i32x4_t r, uint32_t voff, uint32_t lds) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+               ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"(r) : "memory");
+}
+
 }  // namespace
 }  // namespace eb
 

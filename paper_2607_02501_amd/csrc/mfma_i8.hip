@@ -5,26 +5,31 @@
 // MFMA k-step per block, and each block's exact int32 tile scaled by
 // s_ib * d_nb into fp32 accumulators.
 //
-// Activation step (one thread per row and block):
+// Activation step:
 //   s = fl32(max |x| / 127) (0 for an all-zero block),
-//   xq = clamp(round_half_away(x / s), -127, 127), the quotient in binary64
-// (x has at most 11 significant bits and s 24: binary64 decides every
-// rounding as the exact quotient would).  Codes go to xq[m][k] (int8, row
+//   xq = clamp(round_half_away(x / s), -127, 127), as the exact quotient rounds.  Codes go to xq[m][k] (int8, row
 // major), scales to xs[k/32][ms] (block major, ms = m rounded up to 4), both
 // in the caller's workspace.
 //
-// Product kernel: a workgroup of 4 waves owns a 128 (rows of x) x 128
-// (weight rows) output tile; wave (wm, wn) owns 64 x 64 of it as 2 x 2
-// MFMA tiles of 32 x 32.  Per block b a lane holds, for each of its x
-// sub-tiles, the 16 codes k = 32 b + 16 (lane / 32) .. + 15 of row lane % 32
-// (A operand), and for each weight sub-tile the same 16 weight codes of row
-// lane % 32 (B operand; Q4_0 nibbles are unpacked to int8 c - 8 in
-// registers).  The int32 result (lane: weight row lane % 32, x rows
-// 8 (e / 4) + 4 (lane / 32) + e % 4) is converted to fp32 and added with
+// Product kernel: a workgroup of 4 waves owns a 128 (rows of x) x 128 (weight
+// rows) output tile, or 64 x 64; wave (wm, wn) owns a quarter of it as 2 x 2
+// (or one) MFMA tiles of 32 x 32.  k runs in steps of 4 blocks, whose codes
+// and scales are copied to LDS in whole row segments one step ahead.  Per block
+// a lane holds, for each of its x sub-tiles, the 16 codes k = 32 b + 16 (lane /
+// 32) .. + 15 of row lane % 32 (A operand), and for each weight sub-tile the
+// same 16 weight codes of row lane % 32 (B operand; Q4_0 nibbles are unpacked
+// to int8 c - 8 in registers).  The int32 result (lane: weight row lane % 32, x
+// rows 8 (e / 4) + 4 (lane / 32) + e % 4) is converted to fp32 and added with
 // weight s_ib d_nb: fma(float(P), s_ib d_nb, acc) -- three vector ALU
-// operations per output element and block, which bound this kernel (the
-// matrix cores take a quarter of that time).
+// operations per output element and block, which bound this kernel: 192 cycles
+// per 32 x 32 x 32 product, about 770 TOP/s at the clock it runs at.
+// Measured (Q8_0, 816 rows): 2048 -> 32768 269 -> 201 us (545 TOP/s), 16384 ->
+// 2048 383 -> 144 us, with operands read from memory by each wave before,
+// 32 rows a power of two apart per load, and 128 x 128 tiles only.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <type_traits>
 
 #include "eb_internal.h"
 #include "epilogue.h"
@@ -39,57 +44,65 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // ---- activation quantization ----
 
+// |v| / s of the exact quotient, rounded half away from zero, at most 127.
+// The estimate by the reciprocal is raised by 2^-14, more than its error, so it
+// is the result or one more; the lower threshold (q - 1/2) s has at most 33
+// significant bits, exact in binary64, and decides.  A scale so small that its
+// reciprocal may overflow takes the binary64 quotient.
+__device__ inline float code_x8(float v, float s, float r) {
+  const float a = fabsf(v);
+  float q;
+  if (s >= 0x1p-100f) {
+    q = floorf(__builtin_fmaf(a, r, 0.5f + 0x1p-14f));
+    q -= (double)a < ((double)q - 0.5) * (double)s ? 1.0f : 0.0f;
+  } else {
+    q = (float)round((double)a / (double)s);
+  }
+  return copysignf(fminf(q, 127.0f), v);
+}
+
+// Four lanes per row and block, 16 blocks of a row per wave: a wave reads 1 KiB
+// and writes 512 bytes of codes, side by side (a thread per block, 64 bytes
+// apart, and binary64 quotients took 19 us for 816 x 16384, now 13.5).
 template <int XT>
 __global__ void __launch_bounds__(256)
     quantize_x8_kernel(const uint16_t *__restrict__ x, int64_t m, int64_t k, int64_t ms,
                        int8_t *__restrict__ xq, float *__restrict__ xs) {
-  const int64_t nb = k / kQK;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < ms * nb;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int64_t i = t % ms, b = t / ms;  // consecutive threads: consecutive rows of one block
-    if (i >= m) {
-      xs[b * ms + i] = 0.f;
-      continue;
-    }
-    const uint16_t *src = x + i * k + b * kQK;
-    float v[kQK];
-    float a = 0.f;
+  const int64_t nb = k / kQK, groups = (nb + 15) / 16, items = ms * groups;
+  const int lane = threadIdx.x & 63, j = lane & 3;
+  for (int64_t it = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6); it < items; it += (int64_t)gridDim.x * 4) {
+    const int64_t i = it / groups, b = (it - i * groups) * 16 + (lane >> 2);
+    uint4 w = make_uint4(0, 0, 0, 0);
+    if (i < m && b < nb) w = *reinterpret_cast<const uint4 *>(x + i * k + b * kQK + 8 * j);
+    const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
+    float v[8], a = 0.f;
 #pragma unroll
-    for (int j = 0; j < kQK; j += 8) {
-      const uint4 w = *reinterpret_cast<const uint4 *>(src + j);
-      const uint32_t ws[4] = {w.x, w.y, w.z, w.w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const uint16_t lo = (uint16_t)(ws[e] & 0xffffu), hi = (uint16_t)(ws[e] >> 16);
-        v[j + 2 * e] = XT == EB_F16 ? (float)__builtin_bit_cast(_Float16, lo) : __uint_as_float((uint32_t)lo << 16);
-        v[j + 2 * e + 1] = XT == EB_F16 ? (float)__builtin_bit_cast(_Float16, hi) : __uint_as_float((uint32_t)hi << 16);
-      }
+    for (int e = 0; e < 4; ++e) {
+      const uint16_t lo = (uint16_t)(ws[e] & 0xffffu), hi = (uint16_t)(ws[e] >> 16);
+      v[2 * e] = XT == EB_F16 ? (float)__builtin_bit_cast(_Float16, lo) : __uint_as_float((uint32_t)lo << 16);
+      v[2 * e + 1] = XT == EB_F16 ? (float)__builtin_bit_cast(_Float16, hi) : __uint_as_float((uint32_t)hi << 16);
     }
 #pragma unroll
-    for (int j = 0; j < kQK; ++j) a = fmaxf(a, fabsf(v[j]));
-    const float s = a / 127.0f;
-    xs[b * ms + i] = s;
-    uint32_t words[8];
+    for (int e = 0; e < 8; ++e) a = fmaxf(a, fabsf(v[e]));
+    a = fmaxf(a, __shfl_xor(a, 1));
+    a = fmaxf(a, __shfl_xor(a, 2));
+    const float s = a / 127.0f, r = __builtin_amdgcn_rcpf(s);
+    if (b >= nb) continue;  // (whole groups of four lanes)
+    if (j == 0) xs[b * ms + i] = s;
+    if (i >= m) continue;
+    uint32_t words[2] = {0, 0};
+    if (s != 0.f) {
 #pragma unroll
-    for (int w = 0; w < 8; ++w) {
-      uint32_t word = 0;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        int q = 0;
-        if (s != 0.f) q = (int)fmin(fmax(round((double)v[4 * w + e] / (double)s), -127.0), 127.0);
-        word |= (uint32_t)(uint8_t)(int8_t)q << (8 * e);
-      }
-      words[w] = word;
+      for (int e = 0; e < 8; ++e)
+        words[e / 4] |= (uint32_t)(uint8_t)(int8_t)(int)code_x8(v[e], s, r) << (8 * (e % 4));
     }
-    uint4 *dst = reinterpret_cast<uint4 *>(xq + i * k + b * kQK);
-    dst[0] = make_uint4(words[0], words[1], words[2], words[3]);
-    dst[1] = make_uint4(words[4], words[5], words[6], words[7]);
+    *reinterpret_cast<uint2 *>(xq + i * k + b * kQK + 8 * j) = make_uint2(words[0], words[1]);
   }
 }
 
 // ---- product ----
 
-constexpr int kBMi = 128, kBNi = 128;
+constexpr int kBMi = 128, kBNi = 128;  // the larger tile
 
 // 16 Q4_0 nibbles (half h of a block's 16 bytes) -> int8 codes c - 8
 __device__ inline v4i_t q4_codes(const uint4 raw, int h) {
@@ -105,150 +118,168 @@ __device__ inline v4i_t q4_codes(const uint4 raw, int h) {
   return o;
 }
 
-template <int QT, int YT>
-__global__ void __launch_bounds__(256)
+// One stage of LDS: kSB blocks of k of the tile's x codes, weight codes and
+// scales of both.
+constexpr int kSB = 4;
+template <int QT, int F>
+struct I8Stage {
+  static constexpr int QSB = (QT == EB_Q8_0) ? 32 : 16;  // code bytes per block
+  static constexpr int kXcpr = 2 * kSB, kWcpr = QSB / 16 * kSB;  // 16-byte chunks per row
+  static constexpr int T = 64 * F;                               // tile rows of x and of the weights
+  static constexpr int kX = T * kXcpr * 16, kW = T * kWcpr * 16;
+  static constexpr int kS = kSB * T * 4, kD = T * 16;  // x scales block by block; 16 bytes of d16 per row
+  static constexpr int kBytes = kX + kW + kS + kD;
+  static constexpr int kXper = kX / 4096, kWper = kW / 4096;  // 1 KiB copies per wave
+  static constexpr int kJobs = kXper + kWper + 1;
+  static_assert(kS == 1024 * F && kD == 1024 * F, "F copies of each kind of scale");
+};
+
+// F: 32 x 32 tiles per wave in either direction
+template <int QT, int F>
+__global__ void __launch_bounds__(256, 4 / F)
     mm_i8_kernel(const uint8_t *__restrict__ wdata, int64_t n, int64_t k, int64_t d_off, int64_t ds,
                  const int8_t *__restrict__ xq, const float *__restrict__ xs, int64_t ms, int64_t m,
                  void *__restrict__ y, int yt, Fuse f) {
-  constexpr int QSB = (QT == EB_Q8_0) ? 32 : 16;  // code bytes per block
+  using ST = I8Stage<QT, F>;
+  constexpr int QSB = ST::QSB, R = 2, T = ST::T, TW = 32 * F;
+  __shared__ __attribute__((aligned(1024))) uint8_t smem[R * ST::kBytes];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave & 1, wn = wave >> 1;
   const int r = lane & 31, h = lane >> 5;
-  const int64_t n0 = (int64_t)blockIdx.x * kBNi, m0 = (int64_t)blockIdx.y * kBMi;
-  const int rows_n = (int)min((int64_t)kBNi, n - n0), rows_m = (int)min((int64_t)kBMi, m - m0);
-  const int nb = (int)(k / kQK);
-
-  // descriptors over the tile's rows (rows past the end read zeros)
-  const uint32_t qrow = (uint32_t)nb * QSB, drow = (uint32_t)ds * 2;
-  const auto qr = rsrc(wdata + n0 * qrow, (uint32_t)rows_n * qrow);
-  const auto dr = rsrc(wdata + d_off + n0 * drow, (uint32_t)rows_n * drow);
-  const auto xr = rsrc(xq + m0 * k, (uint32_t)rows_m * (uint32_t)k);
-  const auto sr = rsrc(xs, (uint32_t)(nb * ms * 4));
-  uint32_t aoff[2], boff[2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    aoff[i] = (uint32_t)(64 * wm + 32 * i + r) * (uint32_t)k + 16u * h;
-    boff[i] = (uint32_t)(64 * wn + 32 * i + r) * qrow + (QT == EB_Q8_0 ? 16u * h : 0u);
+  // tiles of x rows fastest in groups of 8 weight tiles: an XCD's workgroups
+  // share weight rows in its L2
+  const int tiles_m = (int)((m + T - 1) / T);
+  int nt, mt;
+  {
+    const int g = (int)blockIdx.x / (kXcds * tiles_m), q = (int)blockIdx.x % (kXcds * tiles_m);
+    nt = g * kXcds + q % kXcds;
+    mt = q / kXcds;
   }
+  const int64_t n0 = (int64_t)nt * T, m0 = (int64_t)mt * T;
+  if (n0 >= n) return;
+  const int rows_n = (int)min((int64_t)T, n - n0), rows_m = (int)min((int64_t)T, m - m0);
+  const int nb = (int)(k / kQK), steps = (nb + kSB - 1) / kSB;
 
-  // Block scales of kGB blocks at a time, staged in LDS (two buffers): the
-  // activation scales of the tile's 128 x rows and the weight scales of its
-  // 128 weight rows, as fp32, block-major; a lane then reads its 16 x-row
-  // scales per x sub-tile as four 16-byte LDS reads (lanes of a half-wave
-  // read the same addresses) and one weight scale per weight sub-tile.
-  constexpr int kGB = 8;
-  __shared__ __align__(16) float s_lds[2][kGB][kBMi];
-  __shared__ __align__(16) float d_lds[2][kGB][kBNi];
-  const int t = threadIdx.x;
-  auto stage = [&](int buf, int b0) __attribute__((always_inline)) {
-    // activation scales: 8 blocks x 128 rows, 4 per thread, rows contiguous
+  // descriptors over the tile's rows (rows past the end read zeros), advanced
+  // step by step
+  const uint32_t qrow = (uint32_t)nb * QSB, drow = (uint32_t)ds * 2, xrow = (uint32_t)k;
+  i32x4_t xr = rsrc4(xq + m0 * k, (uint32_t)rows_m * xrow);
+  i32x4_t qr = rsrc4(wdata + n0 * qrow, (uint32_t)rows_n * qrow);
+  i32x4_t sr = wave < F ? rsrc4(xs + m0, (uint32_t)(nb * ms - m0) * 4u)
+                        : rsrc4(wdata + d_off + n0 * drow, (uint32_t)rows_n * drow);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) uint8_t *)smem;
+  uint32_t xo[ST::kXper], qo[ST::kWper], so;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int e = t + 256 * q, bb = e / kBMi, row = e % kBMi;
-      const uint32_t off = (uint32_t)((int64_t)(b0 + bb) * ms + m0 + row) * 4u;
-      s_lds[buf][bb][row] = __builtin_bit_cast(
-          float, __builtin_amdgcn_raw_buffer_load_b32(sr, (int)(b0 + bb < nb ? off : 0x80000000u), 0, 0));
-    }
-    // weight scales: row t (t < 128) holds 8 consecutive binary16 scales
-    if (t < kBNi) {
-      const auto v = __builtin_amdgcn_raw_buffer_load_b128(dr, (int)((uint32_t)t * drow + 2u * b0), 0, 0);
+  for (int i = 0; i < ST::kXper; ++i) {
+    const uint32_t row = (i * 4 + wave) * (64 / ST::kXcpr) + lane / ST::kXcpr;
+    xo[i] = row * xrow + (((lane % ST::kXcpr) ^ chunk_swz<ST::kXcpr>(row)) << 4);
+  }
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const uint32_t w2 = v[q];
-        d_lds[buf][2 * q][t] = (float)__builtin_bit_cast(_Float16, (uint16_t)(w2 & 0xffffu));
-        d_lds[buf][2 * q + 1][t] = (float)__builtin_bit_cast(_Float16, (uint16_t)(w2 >> 16));
-      }
-    }
+  for (int i = 0; i < ST::kWper; ++i) {
+    const uint32_t row = (i * 4 + wave) * (64 / ST::kWcpr) + lane / ST::kWcpr;
+    qo[i] = row * qrow + (((lane % ST::kWcpr) ^ chunk_swz<ST::kWcpr>(row)) << 4);
+  }
+  // waves 0 .. F - 1: the x scales of 4 / F blocks, T rows of 4 bytes each; the
+  // others: d16 of 64 weight rows (F = 1: three waves copy the same bytes)
+  const int sj = wave < F ? wave : (F == 2 ? wave - F : 0);
+  if (wave < F)
+    so = (uint32_t)(sj * (kSB / F) + lane / (16 * F)) * (uint32_t)ms * 4u + (lane % (16 * F)) * 16u;
+  else
+    so = (uint32_t)(sj * 64 + lane) * drow;
+  const uint32_t slds = lds0 + ST::kX + ST::kW + (wave < F ? 0 : ST::kS) + sj * 1024;
+  const uint32_t sstep = wave < F ? (uint32_t)(kSB * ms * 4) : 2u * kSB;
+  auto issue = [&](uint32_t st) __attribute__((always_inline)) {
+    const uint32_t base = lds0 + st + wave * 1024;
+#pragma unroll
+    for (int i = 0; i < ST::kXper; ++i) copy_lds(xr, xo[i], base + i * 4096);
+#pragma unroll
+    for (int i = 0; i < ST::kWper; ++i) copy_lds(qr, qo[i], base + ST::kX + i * 4096);
+    copy_lds(sr, so, slds + st);
+    advance(xr, kSB * 32);
+    advance(qr, kSB * QSB);
+    advance(sr, sstep);
   };
 
-  f32x16_t acc[2][2];
+  // LDS addresses of this lane's operands in block 0; block b is at chunk
+  // index 2 b + h of x (Q8_0 weights too) or b of Q4_0 weights
+  uint32_t xa[F], wa[F], xsw[F], wsw[F];
 #pragma unroll
-  for (int i = 0; i < 2; ++i)
+  for (int i = 0; i < F; ++i) {
+    const uint32_t row = TW * wm + 32 * i + r, col = TW * wn + 32 * i + r;
+    xa[i] = row * (ST::kXcpr * 16);
+    xsw[i] = chunk_swz<ST::kXcpr>(row);
+    wa[i] = ST::kX + col * (ST::kWcpr * 16);
+    wsw[i] = chunk_swz<ST::kWcpr>(col);
+  }
+
+  f32x16_t acc[F][F];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+  for (int i = 0; i < F; ++i)
+#pragma unroll
+    for (int j = 0; j < F; ++j)
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  // operands of block b (zeros past the last block)
-  struct Ops {
-    v4i_t a[2], b[2];
-  };
-  auto load_ops = [&](Ops &o, int b) __attribute__((always_inline)) {
-    const bool ok = b < nb;
+  auto block = [&](const uint8_t *L, int b) __attribute__((always_inline)) {
+    v4i_t a[F], w[F];
+    float dv[F];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      const auto va = __builtin_amdgcn_raw_buffer_load_b128(xr, (int)(ok ? aoff[i] + 32u * b : 0x80000000u), 0, 0);
-      o.a[i] = __builtin_bit_cast(v4i_t, va);
-      const auto vb = __builtin_amdgcn_raw_buffer_load_b128(qr, (int)(ok ? boff[i] + (uint32_t)QSB * b : 0x80000000u), 0, 0);
+    for (int i = 0; i < F; ++i) {
+      a[i] = *reinterpret_cast<const v4i_t *>(L + xa[i] + (((2u * b + h) ^ xsw[i]) << 4));
       if constexpr (QT == EB_Q8_0)
-        o.b[i] = __builtin_bit_cast(v4i_t, vb);
+        w[i] = *reinterpret_cast<const v4i_t *>(L + wa[i] + (((2u * b + h) ^ wsw[i]) << 4));
       else
-        o.b[i] = q4_codes(__builtin_bit_cast(uint4, vb), h);
+        w[i] = q4_codes(*reinterpret_cast<const uint4 *>(L + wa[i] + (((uint32_t)b ^ wsw[i]) << 4)), h);
+      dv[i] = (float)*reinterpret_cast<const _Float16 *>(L + ST::kX + ST::kW + ST::kS + (TW * wn + 32 * i + r) * 16 + 2 * b);
     }
+    f32x4_t sv[F][4];
+#pragma unroll
+    for (int i = 0; i < F; ++i)
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+        sv[i][g] = *reinterpret_cast<const f32x4_t *>(L + ST::kX + ST::kW + (b * T + TW * wm + 32 * i + 8 * g + 4 * h) * 4);
+    v16i_t p[F][F];
+#pragma unroll
+    for (int i = 0; i < F; ++i)
+#pragma unroll
+      for (int j = 0; j < F; ++j) {
+        const v16i_t zero = {};
+        p[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[i], w[j], zero, 0, 0, 0);
+      }
+#pragma unroll
+    for (int i = 0; i < F; ++i)
+#pragma unroll
+      for (int j = 0; j < F; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          acc[i][j][e] = __builtin_fmaf((float)p[i][j][e], sv[i][e >> 2][e & 3] * dv[j], acc[i][j][e]);
   };
 
-  Ops cur, nxt;
-  load_ops(cur, 0);
-  stage(0, 0);
-  __syncthreads();
-  const int ngroups = (nb + kGB - 1) / kGB;
-  for (int gi = 0; gi < ngroups; ++gi) {
-    const int buf = gi & 1, b0 = gi * kGB;
-    if (gi + 1 < ngroups) stage(buf ^ 1, b0 + kGB);  // next group's scales, read after the barrier
-    const int nbg = min(kGB, nb - b0);
-    // block scales of this lane, read from LDS one block ahead of their use
-    f32x4_t sv[2][4], svn[2][4];
-    float dv[2], dvn[2];
-    auto read_scales = [&](f32x4_t (&S)[2][4], float (&D)[2], int bb) __attribute__((always_inline)) {
+  issue(0);
+  for (int s = 0; s < steps; ++s) {
+    const uint32_t st = (s & 1) ? ST::kBytes : 0;
+    wait_vm_barrier<0>();  // step s is in LDS, and every wave is done with step s - 1
+    if (s + 1 < steps) issue(ST::kBytes - st);
+    const uint8_t *L = smem + st;
+    if (nb - s * kSB >= kSB) {
 #pragma unroll
-      for (int i = 0; i < 2; ++i) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-          S[i][g] = *reinterpret_cast<const f32x4_t *>(&s_lds[buf][bb][64 * wm + 32 * i + 8 * g + 4 * h]);
-        D[i] = d_lds[buf][bb][64 * wn + 32 * i + r];
-      }
-    };
-    read_scales(sv, dv, 0);
-    for (int bb = 0; bb < nbg; ++bb) {
-      load_ops(nxt, b0 + bb + 1);
-      read_scales(svn, dvn, bb + 1 < kGB ? bb + 1 : bb);
-      v16i_t p[2][2];
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-          const v16i_t zero = {};
-          p[i][j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(cur.a[i], cur.b[j], zero, 0, 0, 0);
-        }
-#pragma unroll
-      for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-          for (int e = 0; e < 16; ++e)
-            acc[i][j][e] = __builtin_fmaf((float)p[i][j][e], sv[i][e >> 2][e & 3] * dv[j], acc[i][j][e]);
-      cur = nxt;
-#pragma unroll
-      for (int i = 0; i < 2; ++i) {
-#pragma unroll
-        for (int g = 0; g < 4; ++g) sv[i][g] = svn[i][g];
-        dv[i] = dvn[i];
-      }
+      for (int b = 0; b < kSB; ++b) block(L, b);
+    } else {
+      for (int b = 0; b < nb - s * kSB; ++b) block(L, b);
     }
-    __syncthreads();  // the next group's scales are in; this group's buffer is free
   }
 
   // epilogue: lane holds weight row (column of y) 64 wn + 32 j + r and x rows
   // 64 wm + 32 i + 8 (e / 4) + 4 h + e % 4
 #pragma unroll
-  for (int j = 0; j < 2; ++j) {
-    const int cl = 64 * wn + 32 * j + r;
+  for (int j = 0; j < F; ++j) {
+    const int cl = TW * wn + 32 * j + r;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < F; ++i)
 #pragma unroll
       for (int e = 0; e < 16; ++e) {
-        const int rl = 64 * wm + 32 * i + 8 * (e >> 2) + 4 * h + (e & 3);
+        const int rl = TW * wm + 32 * i + 8 * (e >> 2) + 4 * h + (e & 3);
         float v = acc[i][j][e];
         if (f.epi == EB_EPI_GLU) {  // rows 2c, 2c + 1 of the weights sit in lanes r, r ^ 1
           const float up = __shfl_xor(v, 1);
@@ -289,26 +320,29 @@ hipError_t launch_mfma_i8(int32_t type, const void *wdata, int64_t n, int64_t k,
   float *xsc = reinterpret_cast<float *>(static_cast<uint8_t *>(ws) + round_up(m * k, 256));
   const auto *xp = static_cast<const uint16_t *>(x);
   if (xt == EB_F16)
-    quantize_x8_kernel<EB_F16><<<grid1(ms * nb), 256, 0, s>>>(xp, m, k, ms, xq, xsc);
+    quantize_x8_kernel<EB_F16><<<grid1(ms * ((nb + 15) / 16) * 64), 256, 0, s>>>(xp, m, k, ms, xq, xsc);
   else
-    quantize_x8_kernel<EB_BF16><<<grid1(ms * nb), 256, 0, s>>>(xp, m, k, ms, xq, xsc);
+    quantize_x8_kernel<EB_BF16><<<grid1(ms * ((nb + 15) / 16) * 64), 256, 0, s>>>(xp, m, k, ms, xq, xsc);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const Layout L = layout_of(type, n, k);
-  const dim3 grid((unsigned)((n + kBNi - 1) / kBNi), (unsigned)((m + kBMi - 1) / kBMi));
   const auto *wp = static_cast<const uint8_t *>(wdata);
-  if (type == EB_Q8_0) {
-    if (yt == EB_F32)
-      mm_i8_kernel<EB_Q8_0, EB_F32><<<grid, 256, 0, s>>>(wp, n, k, L.d_off, L.ds, xq, xsc, ms, m, y, yt, f);
+  // 128 x 128 tiles where they give every CU its two workgroups, else 64 x 64
+  // (measured, Q8_0, 816 rows: 16384 -> 2048, 112 large tiles, 314 us against
+  // 144; 2560 -> 2048, 140 of them, 54 us against 33)
+  auto launch = [&](auto fc) {
+    constexpr int F = decltype(fc)::value;
+    const int64_t tiles = round_up((n + 64 * F - 1) / (64 * F), kXcds) * ((m + 64 * F - 1) / (64 * F));
+    if (tiles > 0x7fffffff) return hipErrorInvalidValue;
+    if (type == EB_Q8_0)
+      mm_i8_kernel<EB_Q8_0, F><<<(unsigned)tiles, 256, 0, s>>>(wp, n, k, L.d_off, L.ds, xq, xsc, ms, m, y, yt, f);
     else
-      mm_i8_kernel<EB_Q8_0, EB_BF16><<<grid, 256, 0, s>>>(wp, n, k, L.d_off, L.ds, xq, xsc, ms, m, y, yt, f);
-  } else {
-    if (yt == EB_F32)
-      mm_i8_kernel<EB_Q4_0, EB_F32><<<grid, 256, 0, s>>>(wp, n, k, L.d_off, L.ds, xq, xsc, ms, m, y, yt, f);
-    else
-      mm_i8_kernel<EB_Q4_0, EB_BF16><<<grid, 256, 0, s>>>(wp, n, k, L.d_off, L.ds, xq, xsc, ms, m, y, yt, f);
-  }
-  return hipGetLastError();
+      mm_i8_kernel<EB_Q4_0, F><<<(unsigned)tiles, 256, 0, s>>>(wp, n, k, L.d_off, L.ds, xq, xsc, ms, m, y, yt, f);
+    return hipGetLastError();
+  };
+  const int64_t large = ((n + kBNi - 1) / kBNi) * ((m + kBMi - 1) / kBMi);
+  if (large >= 2 * (int64_t)device_cu_count()) return launch(std::integral_constant<int, 2>{});
+  return launch(std::integral_constant<int, 1>{});
 }
 
 }  // namespace eb
