@@ -141,6 +141,7 @@ hipError_t launch_gemv_m1_multi(int32_t type, int32_t xt, int ns, const M1Op *de
 // (partial sums, summed in order by a second kernel).
 struct RowsTiles {        // small-m kernel: 16 nt weight rows x 16 mb rows of x per workgroup
   int nt = 0, mb = 0;
+  int w = 8;              // waves
   int splits = 1;         // of k
   int64_t ws_stride = 0;  // floats between the partial outputs of two splits
 };
@@ -246,7 +247,8 @@ struct MMOp {
   Fuse f;
 };
 constexpr int64_t kMMaxK = int64_t(1) << 22;  // k < this keeps per-tile byte spans in 31 bits
-constexpr int64_t kRowsMaxM = 128;
+constexpr int64_t kRowsMaxM = 128;        // and beyond, up to
+constexpr double kRowsMaxFlops = 9e9;     // this much work
 constexpr int kRowsMaxSplits = 8;
 bool rows_fits(int64_t m, int64_t n, int64_t k);
 // Tile and split of k of a lone projection; partial sums take at most max_ws bytes.

@@ -1,5 +1,5 @@
-// mfma_rows.h -- small-m projections (m <= 128; action-chunk denoising,
-// several robots or speculated tokens) on the matrix cores, Q8_0 and Q4_0:
+// mfma_rows.h -- small projections (m <= 128, or more rows of small matrices;
+// action-chunk denoising, several robots or speculated tokens) on the matrix cores, Q8_0 and Q4_0:
 // the kernel of lone projections and the one of fused runs of independent
 // ones (paper section 3.2: latency-first batch-1 execution, operator fusion;
 // the action-expert projections of section 2.1 / Table 1).  Included only by
@@ -398,15 +398,20 @@ __global__ void __launch_bounds__(W * 64)
 }
 
 // one launch of the tile (NT, MB); splits of k write partial sums to sp.ws
-template <int QT, int XT, int NT, int MB>
+template <int QT, int XT, int NT, int MB, int W = 8>
 hipError_t launch_lone(const MMOp &op, int splits, float *ws, int64_t ws_stride, hipStream_t s) {
-  constexpr int W = 8, R = 3;
+  constexpr int R = 3;
   MMOp o = op;
   o.tiles_n = (o.n + 16 * NT - 1) / (16 * NT);
   const int tiles_m = (o.m + 16 * MB - 1) / (16 * MB);
   const dim3 grid((unsigned)(round_up(o.tiles_n, kXcds) * tiles_m), (unsigned)splits);
   mm_rows_kernel<QT, XT, NT, MB, W, R><<<grid, W * 64, 0, s>>>(o, tiles_m, splits, ws, ws_stride);
   return hipGetLastError();
+}
+
+template <int QT, int XT, int NT, int MB>
+hipError_t launch_lone4(const MMOp &op, int splits, float *ws, int64_t ws_stride, hipStream_t s) {
+  return launch_lone<QT, XT, NT, MB, 4>(op, splits, ws, ws_stride, s);
 }
 
 template <int QT, int XT, int NT, int MB>
@@ -429,6 +434,7 @@ hipError_t rows_lone_x(const RowsTiles &t, const MMOp &o, int splits, float *ws,
                        hipStream_t s) {
   if (t.nt == 1) return EB_ROWS_MB(launch_lone, 1, t.mb, o, splits, ws, stride, s);
   if (t.nt == 2) return EB_ROWS_MB(launch_lone, 2, t.mb, o, splits, ws, stride, s);
+  if (t.w == 4) return EB_ROWS_MB(launch_lone4, 4, t.mb, o, splits, ws, stride, s);
   return EB_ROWS_MB(launch_lone, 4, t.mb, o, splits, ws, stride, s);
 }
 

@@ -1,4 +1,4 @@
-"""The small-m matrix-core kernel (m <= 128, Q8_0 / Q4_0) at the edges of its
+"""The small-m matrix-core kernel (m <= 128, or little work; Q8_0 / Q4_0) at the edges of its
 tiles: 16-row blocks of x and of the weights, one to four of either per
 workgroup, k in steps of eight (lone) or four (long fused runs) 32-weight
 blocks, splits of k.
@@ -38,6 +38,7 @@ FORMATS = [("q8_0", torch.bfloat16), ("q8_0", torch.float16), ("q4_0", torch.bfl
     (2, 1, 32), (16, 15, 224), (17, 16, 256), (33, 17, 288), (48, 33, 544),   # fewer columns than CUs: split k
     (49, 3001, 1504), (64, 4097, 256), (65, 2049, 288), (77, 3008, 96),       # one or two row tiles
     (100, 8191, 288), (128, 8193, 224), (128, 16400, 64), (31, 20000, 64),    # wide tiles of the weights
+    (129, 1000, 288), (300, 1025, 96), (816, 2560, 160), (700, 4097, 32),     # more rows, tiles of four waves
 ])
 def test_rows_lone(eb, oracle, qtype, xdtype, m, n, k):
     w = W.normal((n, k), 7 * n + k, "cpu", W.WEIGHT_STD)
