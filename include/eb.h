@@ -107,7 +107,7 @@ typedef int32_t eb_status;
 
 /* kernel paths for eb_qlinear_ex */
 #define EB_PATH_AUTO 0 /* pick by m, qtype and shape (measured crossover) */
-#define EB_PATH_GEMV 1 /* bandwidth-bound GEMV, requires m <= 8 and m' * k <= 65536, m' = m rounded up to 1, 2, 4 or 8 */
+#define EB_PATH_GEMV 1 /* bandwidth-bound, no workspace, requires m <= 8 and m' * k <= 65536, m' = m rounded up to 1, 2, 4 or 8 */
 #define EB_PATH_MFMA 2 /* LDS-tiled dequantize-to-16-bit + MFMA, any m */
 /* Low-precision prefill variant (section 3.2, backend-specific dispatch), Q8_0 /
  * Q4_0, opt-in only (EB_PATH_AUTO never takes it): x is quantized per

@@ -989,9 +989,32 @@ hipError_t launch_gemv_m1_multi(int32_t type, int32_t xt, int ns, const M1Op *de
   return launch_multi_q<EB_Q8_0, EB_BF16>(dev_ops, nops, units, rows, ns, s);
 }
 
+// Several rows without a normalisation to fuse (which the small-m kernel takes
+// as normalised activations in a workspace, and this path has none): whether
+// the small-m matrix-core kernel reads the weights faster than gemv_kernel,
+// whose lanes read their own x from LDS for every row of the weights.
+// Measured (us, gemv_kernel against it): 5 to 8 rows everywhere (Q4_0 binary16
+// 4096 -> 11008 26.5 against 11.2, Q8_0 bfloat16 50 against 15.6); Q8_0 at 3
+// and 4 rows everywhere (4096 -> 4096 15.4 against 7.5, -> 22016 34 against
+// 30), at 2 rows up to 12288 weight rows (17.4 against 15.5 there, 23 against
+// 29.5 at 22016); Q4_0 only with k of 4096 or more: at 3 and 4 rows binary16
+// (4096 -> 11008 12.8 against 11.2) or up to 8192 weight rows (bfloat16 4096
+// -> 4096 10.4 against 8.2, -> 11008 14.0 against 14.6), at 2 rows up to 8192.
+// Too few workgroups (Q4_0 4096 -> 256 7.2 against 7.9) or steps of k (Q8_0
+// 128 -> 4096 3.1 against 3.2) leave it behind at up to 4 rows.
+bool rows_reads_faster(int32_t type, int32_t xt, int64_t m, int64_t n, int64_t k) {
+  if (m < 2 || !rows_fits(m, n, k)) return false;
+  if (m > 4) return true;
+  if (type == EB_Q8_0) return k >= 512 && (m > 2 || n <= 12288);
+  return k >= 4096 && n >= 1024 && (n <= 8192 || (m > 2 && xt == EB_F16));
+}
+
 hipError_t launch_gemv(int32_t type, const void *wdata, int64_t n, int64_t k, const void *x,
                        int32_t xt, int64_t m, void *y, int32_t yt, const Fuse &f, hipStream_t s) {
   if (type == EB_Q6_S) return launch_gemv_q6(wdata, n, k, x, xt, m, y, yt, f, s);
+  if (f.pro == EB_PRO_NONE && rows_reads_faster(type, xt, m, n, k))
+    return launch_rows(type, xt, rows_plan(m, n, k, 0, device_cu_count()),
+                       rows_op(type, wdata, n, k, x, m, y, yt, f), nullptr, s);
   if (type == EB_Q4_0) {
     if (xt == EB_F16) return launch_m<EB_Q4_0, EB_F16>(wdata, n, k, x, m, y, yt, f, s);
     return launch_m<EB_Q4_0, EB_BF16>(wdata, n, k, x, m, y, yt, f, s);

@@ -14,8 +14,11 @@ namespace {
 // Estimated time (us) of a lone launch: a launch and its first copies, then
 // for every round of workgroups over the CUs its steps of k (one block per
 // wave), each with a part for the rows of x, for the weight rows and for their
-// product.  Tiles of eight waves have a CU to themselves; of those of four
-// (NT = 4) two share one.  Fitted to launches of 1024..4096 -> 1024..8192 at
+// product.  Most tiles of eight waves have a CU to themselves; of those of four
+// (NT = 4) two share one, and of those of at most 16 rows and 32 weight rows
+// three or more, which then take turns at 0.85 of a round each without the last
+// one's idle CUs (Q8_0 11008 x 4096 at 2 to 16 rows: 64-row tiles of the weights
+// 14.0 to 15.2 us, 32-row ones 12.8 to 13.8).  Fitted to launches of 1024..4096 -> 1024..8192 at
 // 16 to 816 rows (Q8_0, bfloat16): within 15%, and it ranks the tiles as the
 // measurements do.
 double lone_us(const RowsTiles &t, int64_t m, int64_t n, int64_t k, int cus) {
@@ -24,7 +27,9 @@ double lone_us(const RowsTiles &t, int64_t m, int64_t n, int64_t k, int cus) {
   double us = 3.0;
   if (t.w == 8) {
     const double step = 0.115 + 0.05 * t.mb + 0.105 * t.nt + 0.02 * t.nt * t.mb;
-    us += (double)((units + cus - 1) / cus) * (double)per * step;
+    double rounds = (double)((units + cus - 1) / cus);
+    if (t.mb == 1 && t.nt <= 2) rounds = std::max(1.0, 0.85 * (double)units / cus);
+    us += rounds * (double)per * step;
   } else {
     const int64_t rounds = (units + 2 * cus - 1) / (2 * cus);
     const double step = (0.3 + 0.17 * t.mb) * (units <= cus ? 0.7 : 1.0);

@@ -81,3 +81,29 @@ def test_rows_fused_run(eb, oracle, qtype, xdtype, shapes):
             assert_parity(y, y_ref, bound, tol(k), f"rows_fused {qtype} k={k}")
             y.fill_(7.0)
     eb.stack_cache_clear()
+
+
+@pytest.mark.parametrize("qtype,xdtype", FORMATS)
+@pytest.mark.parametrize("m,n,k", [
+    (2, 4096, 4096), (2, 4097, 4064), (2, 12289, 64), (3, 8193, 4096), (4, 8192, 4128),  # both sides of the rule
+    (3, 17, 32), (5, 1, 32), (7, 4099, 2080), (8, 33, 8192),
+])
+def test_gemv_of_several_rows(eb, oracle, qtype, xdtype, m, n, k):
+    """The bandwidth path at 2 to 8 rows, on either side of the rule that
+    takes it to this kernel, with no workspace and each epilogue."""
+    w = W.normal((n, k), 5 * n + k, "cpu", W.WEIGHT_STD)
+    x = W.normal((m, k), 13 * m + k, "cpu").to(xdtype)
+    qw, xd = eb.quantize(w.to(DEV), qtype), x.to(DEV)
+    _, y_ref, bound = oracle_reference(oracle, qtype, w.numpy(), x)
+    y = eb.qlinear(qw, xd, path="gemv")
+    assert_parity(y, y_ref, bound, tol(k), f"rows_gemv {qtype} m={m} n={n} k={k}")
+    r = W.normal((m, n), 17 * n + m, "cpu")
+    got = eb.qlinear_fused(qw, xd, epilogue="add", residual=r.to(DEV), path="gemv")
+    # the epilogues act on the same fp32 sums, in one rounding each
+    torch.testing.assert_close(got, y + r.to(DEV), rtol=0, atol=0)
+    if n % 2 == 0:
+        z = y.double()
+        want = z[:, 0::2] / (1 + torch.exp(-z[:, 0::2])) * z[:, 1::2]
+        got = eb.qlinear_fused(qw, xd, epilogue="glu", path="gemv")
+        # silu and the product in fp32, the exponential to 2^-21: 2^-19 of the result covers both
+        torch.testing.assert_close(got.double(), want, rtol=2.0 ** -19, atol=1e-30)
