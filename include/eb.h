@@ -259,8 +259,9 @@ eb_status eb_qlinear_fused_static(const eb_qlinear_op *op, int32_t path, hipStre
  * No bias.  Accuracy, with B = sum_k |x||w_hat| per output (plus the output
  * rounding when y_type is 16-bit):
  *   - GEMV path (m <= 8), any x_type: |y - y_exact| <= 2e-3 B;
- *   - MFMA path, EB_BF16 x, m <= 128: w_hat enters the matrix cores as a pair
- *     of bfloat16 values (hi + lo, within 2^-16 of w_hat): <= 2e-3 B;
+ *   - MFMA path, EB_BF16 x, m <= 128: the codes enter the matrix cores as exact
+ *     integers, scaled per block in fp32 (Q6_S, and tiles forced by
+ *     eb_qlinear_tuned: w_hat as hi + lo, within 2^-16): <= 2e-3 B;
  *   - MFMA path, EB_BF16 x, m > 128 (matrix-core bound): w_hat is rounded once
  *     to bfloat16 (8 significant bits): <= (2e-3 + 2^-8) B;
  *   - MFMA path, EB_F16 x: w_hat is rounded once to binary16 (11 significant
