@@ -392,12 +392,16 @@ def qlinear_stack(ops: ctypes.Array, device=None) -> None:
         if st != EB_ERR_INVALID:
             return _check(st, "eb_qlinear_stack")
     nbytes = stack_workspace_bytes(ops)
-    if nbytes and (ws is None or ws is False or ws.numel() < nbytes):
-        ws = torch.empty(nbytes, dtype=torch.uint8,
-                         device=device if device is not None else torch.cuda.current_device())
-    ops._eb_workspace = ws if nbytes else False
-    wp, wb = (ws.data_ptr(), ws.numel()) if nbytes else (None, 0)
+    wp, wb = None, 0
+    if nbytes:
+        if ws is None or ws is False or ws.numel() < nbytes:
+            ws = torch.empty(nbytes, dtype=torch.uint8,
+                             device=device if device is not None else torch.cuda.current_device())
+            ops._eb_workspace = ws
+        wp, wb = ws.data_ptr(), ws.numel()
     _check(lib.eb_qlinear_stack(ops, len(ops), wp, wb, stream), "eb_qlinear_stack")
+    if ws is None:  # (a list refused as invalid also asks for 0 bytes: a workspace there is stays)
+        ops._eb_workspace = False
 
 
 def stack_launches(ops: ctypes.Array) -> int:
