@@ -382,26 +382,26 @@ def stack_workspace_bytes(ops: ctypes.Array) -> int:
 def qlinear_stack(ops: ctypes.Array, device=None) -> None:
     """eb_qlinear_stack with a workspace that belongs to this op array (kept
     on it: the cached plan keeps its tables there while it is cached).  Its size
-    takes a plan on the host to tell, so it is asked for on the first call and
-    when the library finds the workspace too small (ops changed since)."""
+    takes a plan on the host to tell, so it is asked for when the array's
+    contents have changed since the last call (0.8 us to see for 128 ops), and
+    when the library finds the workspace too small (EB_STACK_* changed since)."""
     stream = _stream(device)
+    seen = bytes(ops)
     ws = getattr(ops, "_eb_workspace", None)
-    if ws is not None:
-        wp, wb = (ws.data_ptr(), ws.numel()) if ws is not False else (None, 0)
+    sized, nbytes = getattr(ops, "_eb_sized", (None, 0))
+    if sized == seen:
+        wp, wb = (ws.data_ptr(), ws.numel()) if nbytes else (None, 0)
         st = lib.eb_qlinear_stack(ops, len(ops), wp, wb, stream)
         if st != EB_ERR_INVALID:
             return _check(st, "eb_qlinear_stack")
-    nbytes = stack_workspace_bytes(ops)
-    wp, wb = None, 0
-    if nbytes:
-        if ws is None or ws is False or ws.numel() < nbytes:
-            ws = torch.empty(nbytes, dtype=torch.uint8,
-                             device=device if device is not None else torch.cuda.current_device())
-            ops._eb_workspace = ws
-        wp, wb = ws.data_ptr(), ws.numel()
+    nbytes = stack_workspace_bytes(ops)  # (0 too for a list that will be refused)
+    if nbytes and (ws is None or ws.numel() < nbytes):
+        ws = torch.empty(nbytes, dtype=torch.uint8,
+                         device=device if device is not None else torch.cuda.current_device())
+        ops._eb_workspace = ws
+    wp, wb = (ws.data_ptr(), ws.numel()) if nbytes else (None, 0)
     _check(lib.eb_qlinear_stack(ops, len(ops), wp, wb, stream), "eb_qlinear_stack")
-    if ws is None:  # (a list refused as invalid also asks for 0 bytes: a workspace there is stays)
-        ops._eb_workspace = False
+    ops._eb_sized = (seen, nbytes)
 
 
 def stack_launches(ops: ctypes.Array) -> int:

@@ -71,3 +71,35 @@ def test_rejected_first_call_and_no_workspace(stack):
     ops[0].m = 2  # and now some
     eb.qlinear_stack(ops, "cpu")
     assert fake.calls[-1] == (ops._eb_workspace.data_ptr(), 2048)
+
+
+def test_changed_ops_ask_for_their_size_before_the_call(stack):
+    """Under a stream capture the library runs the ops plainly and takes any
+    workspace (an op may then run unsplit or be refused), so a list that has
+    grown gets its larger workspace before it is passed on, not on an error."""
+    eb, fake = stack
+    ops = _ops(eb, 1, 0)
+    eb.qlinear_stack(ops, "cpu")
+    asked = []
+    size = fake.eb_qlinear_stack_workspace_bytes
+    fake.eb_qlinear_stack_workspace_bytes = lambda o, n: asked.append(1) or size(o, n)
+    eb.qlinear_stack(ops, "cpu")
+    assert not asked  # the same ops: the size is known
+    n = len(fake.calls)
+    ops[1].m = 5
+    eb.qlinear_stack(ops, "cpu")
+    assert [wb for _, wb in fake.calls[n:]] == [6144]
+    ops[1].m = 0  # smaller again: the larger workspace serves
+    eb.qlinear_stack(ops, "cpu")
+    assert fake.calls[-1][1] == 6144
+
+
+def test_too_small_for_another_setting_is_asked_again(stack):
+    """The EB_STACK_* settings change what the same ops need."""
+    eb, fake = stack
+    ops = _ops(eb, 2)
+    eb.qlinear_stack(ops, "cpu")
+    need = fake._need
+    fake._need = lambda o, n: 2 * need(o, n)
+    eb.qlinear_stack(ops, "cpu")
+    assert fake.calls[-1] == (ops._eb_workspace.data_ptr(), 4096)
