@@ -379,6 +379,19 @@ def stack_workspace_bytes(ops: ctypes.Array) -> int:
     return int(lib.eb_qlinear_stack_workspace_bytes(ops, len(ops)))
 
 
+def _array_workspace(arr: ctypes.Array, nbytes: int, device) -> torch.Tensor:
+    """The workspace kept on an op or module array, of at least nbytes.  One that
+    it has outgrown stays on the array too: a cached plan may have its tables there."""
+    ws = getattr(arr, "_eb_workspace", None)
+    if ws is None or ws.numel() < nbytes:
+        if ws is not None:
+            arr._eb_outgrown = getattr(arr, "_eb_outgrown", ()) + (ws,)
+        ws = torch.empty(nbytes, dtype=torch.uint8,
+                         device=device if device is not None else torch.cuda.current_device())
+        arr._eb_workspace = ws
+    return ws
+
+
 def qlinear_stack(ops: ctypes.Array, device=None) -> None:
     """eb_qlinear_stack with a workspace that belongs to this op array (kept
     on it: the cached plan keeps its tables there while it is cached).  Its size
@@ -387,18 +400,15 @@ def qlinear_stack(ops: ctypes.Array, device=None) -> None:
     when the library finds the workspace too small (EB_STACK_* changed since)."""
     stream = _stream(device)
     seen = bytes(ops)
-    ws = getattr(ops, "_eb_workspace", None)
     sized, nbytes = getattr(ops, "_eb_sized", (None, 0))
     if sized == seen:
+        ws = ops._eb_workspace if nbytes else None
         wp, wb = (ws.data_ptr(), ws.numel()) if nbytes else (None, 0)
         st = lib.eb_qlinear_stack(ops, len(ops), wp, wb, stream)
         if st != EB_ERR_INVALID:
             return _check(st, "eb_qlinear_stack")
     nbytes = stack_workspace_bytes(ops)  # (0 too for a list that will be refused)
-    if nbytes and (ws is None or ws.numel() < nbytes):
-        ws = torch.empty(nbytes, dtype=torch.uint8,
-                         device=device if device is not None else torch.cuda.current_device())
-        ops._eb_workspace = ws
+    ws = _array_workspace(ops, nbytes, device) if nbytes else None
     wp, wb = (ws.data_ptr(), ws.numel()) if nbytes else (None, 0)
     _check(lib.eb_qlinear_stack(ops, len(ops), wp, wb, stream), "eb_qlinear_stack")
     ops._eb_sized = (seen, nbytes)
@@ -435,11 +445,7 @@ def make_modules(specs) -> ctypes.Array:
 def multirate_tick(mods: ctypes.Array, tick: int, device=None) -> None:
     """eb_multirate_tick with a workspace that belongs to this module array."""
     nbytes = int(lib.eb_multirate_workspace_bytes(mods, len(mods)))
-    ws = getattr(mods, "_eb_workspace", None)
-    if nbytes and (ws is None or ws.numel() < nbytes):
-        ws = torch.empty(nbytes, dtype=torch.uint8,
-                         device=device if device is not None else torch.device("cuda"))
-        mods._eb_workspace = ws
+    ws = _array_workspace(mods, nbytes, device) if nbytes else getattr(mods, "_eb_workspace", None)
     dev = ws.device if ws is not None else torch.device("cuda")
     _check(lib.eb_multirate_tick(mods, len(mods), tick, ws.data_ptr() if nbytes else None, nbytes,
                                  _stream(dev)), "eb_multirate_tick")

@@ -3,6 +3,8 @@ libeb.so and records the workspace each call gets.  A cached plan keeps its
 launch tables in the workspace that its call passed, so that memory stays with
 the op array for as long as the array lives."""
 
+import weakref
+
 import pytest
 
 
@@ -103,3 +105,28 @@ def test_too_small_for_another_setting_is_asked_again(stack):
     fake._need = lambda o, n: 2 * need(o, n)
     eb.qlinear_stack(ops, "cpu")
     assert fake.calls[-1] == (ops._eb_workspace.data_ptr(), 4096)
+
+
+def test_an_outgrown_workspace_stays_with_the_array(stack):
+    """The plan of the smaller list is still cached and has its tables there."""
+    eb, fake = stack
+    ops = _ops(eb, 1)
+    eb.qlinear_stack(ops, "cpu")
+    first = weakref.ref(ops._eb_workspace)
+    ops[0].m = 4
+    eb.qlinear_stack(ops, "cpu")
+    assert ops._eb_workspace.numel() == 4096 and first() is not None
+    del ops
+    assert first() is None
+
+
+def test_an_outgrown_tick_workspace_stays_with_the_modules(stack):
+    eb, fake = stack
+    mods, need = eb.make_modules([(_ops(eb, 1), 1, 0, 1)]), [1024]
+    fake.eb_multirate_workspace_bytes = lambda m, n: need[0]
+    fake.eb_multirate_tick = lambda m, n, tick, wp, wb, stream: eb.EB_OK
+    eb.multirate_tick(mods, 0, "cpu")
+    first = weakref.ref(mods._eb_workspace)
+    need[0] = 2048
+    eb.multirate_tick(mods, 1, "cpu")
+    assert mods._eb_workspace.numel() == 2048 and first() is not None
