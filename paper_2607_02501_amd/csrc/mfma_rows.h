@@ -92,6 +92,29 @@ __device__ inline uint4 codes8(uint2 q, bool hi) {
   return make_uint4(a.x, a.y, b.x, b.y);
 }
 
+// Blocks [b0, b1) of one output as sums of x * w_hat (exact products).  The
+// matrix cores add 32 products with the integer codes before the block's scale
+// comes in, which bfloat16 activations above 3.4e38 / (32 * 128) = 8e34 can take
+// past the range of fp32 although the output is within it (or the scale is
+// zero); such sums are not finite, and their outputs are computed again here.
+template <int QT>
+__device__ inline float plain_output(const MMOp &o, int64_t row, int64_t col, int b0, int b1) {
+  constexpr int QSB = (QT == EB_Q8_0) ? 32 : 16;
+  const uint16_t *x = o.x + row * o.k;
+  const uint8_t *q = o.w + col * (o.k / kQK) * QSB;
+  const _Float16 *d = reinterpret_cast<const _Float16 *>(o.w + o.d_off) + col * o.ds;
+  float acc = 0.f;
+#pragma unroll 1
+  for (int b = b0; b < b1; ++b) {
+#pragma unroll 1
+    for (int j = 0; j < kQK; ++j) {
+      const int c = QT == EB_Q8_0 ? (int)(int8_t)q[b * 32 + j] : (q[b * 16 + (j & 15)] >> (j & 16 ? 4 : 0) & 15) - 8;
+      acc = __builtin_fmaf(__uint_as_float((uint32_t)x[b * kQK + j] << 16), (float)c * (float)d[b], acc);
+    }
+  }
+  return acc;
+}
+
 template <int QT, int NT, int MB, int W, int R>
 struct RowsTile {
   static constexpr int kXcpr = 4 * W;                               // 16-byte chunks per staged row of x
@@ -289,28 +312,43 @@ __device__ inline void rows_unit(const MMOp &o, int nt, int mt, int sp, int spli
       for (int b = 0; b < MB; ++b) mine[(i * MB + b) * 64 + lane] = acc[i][b];
   }
   __syncthreads();
-  auto sum = [&](int u) __attribute__((always_inline)) {
+  f32x4_t v[EPT];
+#pragma unroll
+  for (int u = 0; u < EPT; ++u) {
     const int e = t + u * W * 64;
-    f32x4_t v = {0.f, 0.f, 0.f, 0.f};
-    if (ELEMS % (W * 64) != 0 && e >= ELEMS) return v;
-    v = slot(0)[e];
+    v[u] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    if (ELEMS % (W * 64) != 0 && e >= ELEMS) continue;
+    v[u] = slot(0)[e];
 #pragma unroll
     for (int w = 1; w < W; ++w) {
       const f32x4_t a = slot(w)[e];
 #pragma unroll
-      for (int i = 0; i < 4; ++i) v[i] += a[i];
+      for (int i = 0; i < 4; ++i) v[u][i] += a[i];
     }
-    return v;
-  };
+    if constexpr (XT == EB_BF16) {
+      const int l = e & 63, tile = e >> 6;
+      const int cl = 16 * (tile / MB) + (l & 15), rl = 16 * (tile % MB) + 4 * (l >> 4);
+      uint32_t lost = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (!__builtin_isfinite(v[u][i]) && rl + i < rows_m && cl < rows_n) lost |= 1u << i;
+#pragma unroll 1
+      for (; lost; lost &= lost - 1) {
+        const int j = __builtin_ctz(lost);
+        const float r = plain_output<QT>(o, m0 + rl + j, n0 + cl, s0 * W, min(nb, s1 * W));
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (i == j) v[u][i] = r;
+      }
+    }
+  }
   if (ws) {  // a split of k: the raw partial sums, for the ordered reduction
     const auto wr = rsrc(ws + (int64_t)sp * ws_stride + out0, out_n * 4);
 #pragma unroll
-    for (int u = 0; u < EPT; ++u) {
-      const f32x4_t v = sum(u);
+    for (int u = 0; u < EPT; ++u)
 #pragma unroll
       for (int i = 0; i < 4; ++i)
-        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[i]), wr, (int)(el[u][i] * 4), 0, 0);
-    }
+        __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v[u][i]), wr, (int)(el[u][i] * 4), 0, 0);
     return;
   }
   auto put = [&](auto ytc) __attribute__((always_inline)) {
@@ -325,31 +363,25 @@ __device__ inline void rows_unit(const MMOp &o, int nt, int mt, int sp, int spli
     };
     if (glu) {  // the gate/up pair of columns 2c, 2c + 1 sits in lanes l, l ^ 1
 #pragma unroll
-      for (int u = 0; u < EPT; ++u) {
-        const f32x4_t v = sum(u);
+      for (int u = 0; u < EPT; ++u)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const float g = v[i];
+          const float g = v[u][i];
           const float up = __builtin_bit_cast(
               float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, g), 0xB1, 0xF, 0xF, true));
           store(silu_mul(g, up), el[u][i]);
         }
-      }
     } else if (add) {
 #pragma unroll
-      for (int u = 0; u < EPT; ++u) {
-        const f32x4_t v = sum(u);
+      for (int u = 0; u < EPT; ++u)
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-          store(v[i] + (YT == EB_F32 ? res[u][i] : from_y16((uint16_t)__float_as_uint(res[u][i]), YT)), el[u][i]);
-      }
+          store(v[u][i] + (YT == EB_F32 ? res[u][i] : from_y16((uint16_t)__float_as_uint(res[u][i]), YT)), el[u][i]);
     } else {
 #pragma unroll
-      for (int u = 0; u < EPT; ++u) {
-        const f32x4_t v = sum(u);
+      for (int u = 0; u < EPT; ++u)
 #pragma unroll
-        for (int i = 0; i < 4; ++i) store(v[i], el[u][i]);
-      }
+        for (int i = 0; i < 4; ++i) store(v[u][i], el[u][i]);
     }
   };
   if (yt == EB_F32)

@@ -10,7 +10,7 @@ scaling and one addition per block and up to 8 partial tiles, at most
 import pytest
 import torch
 
-from tests.gpu_helpers import assert_parity, oracle_reference
+from tests.gpu_helpers import QT, XT, assert_parity, bits16, oracle_reference
 from paper_2607_02501_amd import workloads as W
 
 pytestmark = pytest.mark.gpu
@@ -107,3 +107,42 @@ def test_gemv_of_several_rows(eb, oracle, qtype, xdtype, m, n, k):
         got = eb.qlinear_fused(qw, xd, epilogue="glu", path="gemv")
         # silu and the product in fp32, the exponential to 2^-21: 2^-19 of the result covers both
         torch.testing.assert_close(got.double(), want, rtol=2.0 ** -19, atol=1e-30)
+
+
+@pytest.mark.parametrize("qtype", ["q8_0", "q4_0"])
+@pytest.mark.parametrize("m,n,k,path", [
+    (50, 40, 1056, "mfma"),      # k split: partial sums
+    (128, 8193, 224, "mfma"),    # wide tiles of the weights
+    (300, 1025, 96, "mfma"),     # more rows
+    (7, 257, 2080, "gemv"),      # the bandwidth path at several rows
+])
+def test_activations_beyond_the_range_of_a_block_sum(eb, oracle, qtype, m, n, k, path):
+    """bfloat16 activations whose sums with the integer codes leave the range of
+    fp32 before the block's scale brings the output back into it, between rows
+    of ordinary ones; and blocks of scale zero with codes, which add nothing.
+    Such outputs are fp32 sums over k of exact products: k 2^-24 of the bound,
+    and as much again for the parts of a split."""
+    w = W.normal((n, k), 3 * n + k, "cpu", W.WEIGHT_STD)
+    x = W.normal((m, k), 19 * m + k, "cpu")
+    x[::3] *= 2.0 ** 125                       # sums with the codes of 2^129 and more, outputs near 2^125
+    x[1] = torch.where(x[1] < 0, -1.0, 1.0) * 3.38e38
+    x = x.to(torch.bfloat16)
+    blocks = oracle.quantize(QT[qtype], w.numpy())
+    blocks[:, 1::3, :2] = 0
+    # row 1 (the largest finite activations) meets scales of 2^-24
+    small = blocks.copy()
+    small[:, 0::3, 0], small[:, 0::3, 1] = 1, 0
+    small[:, 2::3, 0], small[:, 2::3, 1] = 1, 0
+    for b, rows in ((blocks, [i for i in range(m) if i != 1]), (small, [1])):
+        qw = eb.from_canonical(torch.from_numpy(b).to(DEV), qtype, n, k)
+        y_ref, bound = oracle.qlinear(QT[qtype], b, n, k, bits16(x[rows]), XT[x.dtype])
+        bar = 2 * k * 2.0 ** -24 + tol(k)
+        xd = x.to(DEV)
+        y = eb.qlinear(qw, xd, path=path)[rows]
+        assert_parity(y, y_ref, bound, bar, f"rows_range {qtype} m={m} n={n} k={k}")
+        if m <= 128:  # as a fused run
+            out = [torch.zeros(m, n, device=DEV) for _ in range(2)]
+            eb.qlinear_stack(eb.make_ops([(qw, xd, o) for o in out]))
+            for o in out:
+                assert_parity(o[rows], y_ref, bound, bar, f"rows_range_fused {qtype} m={m} n={n} k={k}")
+            eb.stack_cache_clear()
