@@ -34,20 +34,26 @@ __device__ inline float f16_bits_to_f32(uint16_t b) {
   return (float)__builtin_bit_cast(_Float16, b);
 }
 
-// floor(a / d + 1/2) of the exact quotient, plus z, kept within [lo, hi], for
-// d > 0 and r = 1 / d to an ulp or two; c0 = z + 1/2.  The estimate is raised
-// by 2^-14, more than its error where it matters (quotients up to 128 in
-// size: at most 1.5 2^-16), so it is the result or one more, and the lower
-// threshold of that, (q - 1/2) d, is exact in binary32 there.
-__device__ inline float round_half_up(float a, float d, float r, float c0, float lo, float hi) {
+// floor(a / d + 1/2) of the exact quotient, plus z, for d > 0 and r = 1 / d to
+// an ulp or two; c0 = z + 1/2.  The estimate is raised by 2^-14, more than its
+// error where it matters (quotients up to 128 in size: at most 1.5 2^-16), so
+// it is the result or one more, and the lower threshold of that, (q - 1/2) d,
+// is exact in binary32 there.
+__device__ inline float half_up(float a, float d, float r, float c0) {
   float q = floorf(__builtin_fmaf(a, r, c0 + 0x1p-14f));
   q -= a < (q - c0) * d ? 1.0f : 0.0f;
-  return __builtin_amdgcn_fmed3f(q, lo, hi);
+  return q;
 }
 
-// The exact quotient a / d rounded half away from zero, within [-lim, lim].
+// The same kept within [lo, hi]; a quotient that is not a number gives lo.
+__device__ inline float round_half_up(float a, float d, float r, float c0, float lo, float hi) {
+  return __builtin_amdgcn_fmed3f(half_up(a, d, r, c0), lo, hi);
+}
+
+// The exact quotient a / d rounded half away from zero, within [-lim, lim]
+// (-lim if it is not a number).
 __device__ inline int round_half_away(float a, float d, float r, float lim) {
-  return (int)copysignf(round_half_up(fabsf(a), d, r, 0.5f, 0.0f, lim), a);
+  return (int)__builtin_amdgcn_fmed3f(copysignf(half_up(fabsf(a), d, r, 0.5f), a), -lim, lim);
 }
 
 // Zero the alignment gaps of the planar layout: [qs_end, d_off) and
@@ -108,6 +114,7 @@ __global__ void __launch_bounds__(256) quantize_kernel(const float *__restrict__
       float amax = fmaxf(fmaxf(fabsf(e[0]), fabsf(e[1])), fmaxf(fabsf(e[2]), fabsf(e[3])));
 #pragma unroll
       for (int o = 4; o >= 1; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o));
+      amax = fmaxf(amax, 0.0f);  // a block with no number in it counts as zeros
       float d32;
       if constexpr (QT == EB_Q8_0) {
         d32 = amax / 127.0f;

@@ -80,3 +80,69 @@ def test_canonical_at_any_byte_offset(eb, oracle, qtype, n, k):
         assert eb.lib.eb_qweights_from_canonical(eb.QTYPES[qtype], dst.data_ptr() + off, n, k,
                                                  out.buf.data_ptr(), s) == 0
         assert torch.equal(out.buf, qw.buf)
+
+
+def _not_finite(n, k):
+    """Ordinary weights with, by row: one NaN, infinities, a whole block of 32
+    (and of 16) NaNs, a row of them, NaNs among zeros."""
+    w = W.normal((n, k), n + k, "cpu", W.WEIGHT_STD).numpy().copy()
+    w[0, 5] = np.nan
+    w[1, 7], w[1, 70] = np.inf, -np.inf
+    w[2, 32:64] = np.nan
+    w[3, 16:32] = -np.nan
+    w[4, :] = np.nan
+    w[5, :] = 0.0
+    w[5, 3] = np.nan
+    return w
+
+
+def _ieee_blocks(qtype, w):
+    """The formats' definitions in IEEE arithmetic: comparisons and maxima pass
+    NaNs by, and a quotient that is NaN takes the lowest code."""
+    n, k = w.shape
+    with np.errstate(invalid="ignore", divide="ignore", over="ignore"):
+        if qtype == "q6_s":
+            b = w.reshape(n, k // 256, 16, 16)
+            mag = np.where(np.isnan(b), -1.0, np.abs(b))
+            m = np.take_along_axis(b, mag.argmax(-1)[..., None], -1)
+            m = np.where(mag.max(-1, keepdims=True) > 0, m, np.float32(0))
+            s = m / np.float32(-32)
+            d = (np.abs(s).max(2, keepdims=True) / np.float32(127)).astype(np.float16).astype(np.float64)
+            sc = _nearest(s.astype(np.float64), d, -127, 127, away=True)
+            e = d * sc
+            return d, sc, _nearest(b.astype(np.float64), e, -32, 31, away=False)
+        b = w.reshape(n, k // 32, 32)
+        mag = np.where(np.isnan(b), -1.0, np.abs(b))
+        m = np.take_along_axis(b, mag.argmax(-1)[..., None], -1)
+        m = np.where(mag.max(-1, keepdims=True) > 0, m, np.float32(0))
+        d32 = np.abs(m) / np.float32(127) if qtype == "q8_0" else m / np.float32(-8)
+        d = d32.astype(np.float16).astype(np.float64)
+        lo, hi = (-127, 127) if qtype == "q8_0" else (-8, 7)
+        return d, None, _nearest(b.astype(np.float64), d, lo, hi, away=qtype == "q8_0")
+
+
+def _nearest(v, d, lo, hi, away):
+    t = v / d
+    t = np.sign(t) * np.floor(np.abs(t) + 0.5) if away else np.floor(t + 0.5)
+    return np.where(d == 0, 0, np.where(np.isnan(t), lo, np.clip(t, lo, hi)))
+
+
+@pytest.mark.parametrize("qtype", ["q8_0", "q4_0", "q6_s"])
+def test_weights_that_are_not_finite(eb, qtype):
+    n, k = 7, 768
+    w = _not_finite(n, k)
+    got = eb.to_canonical(eb.quantize(torch.from_numpy(w).cuda(), qtype)).cpu().numpy()
+    d, sc, q = _ieee_blocks(qtype, w)
+    nb = k // (256 if qtype == "q6_s" else 32)
+    assert np.array_equal(got[..., :2].copy().view(np.float16)[..., 0].astype(np.float64), d.reshape(n, nb))
+    if qtype == "q8_0":
+        assert np.array_equal(got[..., 2:].view(np.int8), q)
+    elif qtype == "q4_0":
+        codes = np.concatenate([got[..., 2:] & 15, got[..., 2:] >> 4], -1).astype(int) - 8
+        assert np.array_equal(codes, q)
+    else:
+        assert np.array_equal(got[..., 2:18].view(np.int8), sc[..., 0])
+        c = got[..., 18:].reshape(n, nb, 8, 24).astype(int)
+        low = np.concatenate([c[..., :16] & 15, c[..., :16] >> 4], -1)
+        top = np.concatenate([c[..., 16:] >> s & 3 for s in (0, 2, 4, 6)], -1)
+        assert np.array_equal((low | top << 4).reshape(n, nb, 16, 16) - 32, q)
