@@ -44,7 +44,8 @@ typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // ---- activation quantization ----
 
-// |v| / s of the exact quotient, rounded half away from zero, at most 127.
+// v / s of the exact quotient, rounded half away from zero, within [-127, 127];
+// -127 where it is not a number.
 // The estimate by the reciprocal is raised by 2^-14, more than its error, so it
 // is the result or one more; the lower threshold (q - 1/2) s has at most 33
 // significant bits, exact in binary64, and decides.  A scale so small that its
@@ -58,7 +59,7 @@ __device__ inline float code_x8(float v, float s, float r) {
   } else {
     q = (float)round((double)a / (double)s);
   }
-  return copysignf(fminf(q, 127.0f), v);
+  return __builtin_amdgcn_fmed3f(copysignf(q, v), -127.0f, 127.0f);
 }
 
 // Four lanes per row and block, 16 blocks of a row per wave: a wave reads 1 KiB

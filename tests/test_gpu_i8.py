@@ -115,6 +115,24 @@ def test_i8_structured_activations(eb, oracle, kind):
     assert np.all(np.abs(y.double().cpu().numpy() - y16) <= qerr + TOL_F32 * b8 + 1e-30)
 
 
+@pytest.mark.parametrize("xdtype", [torch.float16, torch.bfloat16])
+def test_i8_codes_of_activations_that_are_not_finite(eb, xdtype):
+    """A NaN passes its block's maximum by and takes the code -127, as every
+    quotient that is not a number does; the others in its block keep theirs."""
+    n, k, m = 16, 128, 8
+    x = W.normal((m, k), 1750, "cpu").to(xdtype)
+    qw = eb.quantize(W.normal((n, k), 1751, DEV, W.WEIGHT_STD), "q8_0")
+    x[:, 3] = 9.0                                  # the scales of the first blocks
+    codes = lambda t: _run_i8(eb, qw, t.to(DEV))[1].cpu().numpy()[:m * k].view(np.int8).reshape(m, k)  # noqa: E731
+    want = codes(x).copy()
+    x[0, 5], x[1, 6], x[2, 64:96] = float("nan"), -float("nan"), float("nan")
+    x[3, 40], x[4, 41] = float("inf"), -float("inf")
+    want[0, 5], want[1, 6], want[2, 64:96] = -127, -127, 0
+    want[3:5, 32:64] = 0
+    want[3, 40] = want[4, 41] = -127
+    assert np.array_equal(codes(x), want)
+
+
 def test_i8_refusals(eb):
     qw = eb.quantize(W.normal((64, 512), 1800, DEV, W.WEIGHT_STD), "q6_s")
     x = W.normal((64, 512), 1801, DEV).to(torch.bfloat16)
