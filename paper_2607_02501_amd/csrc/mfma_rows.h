@@ -97,19 +97,30 @@ __device__ inline uint4 codes8(uint2 q, bool hi) {
 // comes in, which bfloat16 activations above 3.4e38 / (32 * 128) = 8e34 can take
 // past the range of fp32 although the output is within it (or the scale is
 // zero); such sums are not finite, and their outputs are computed again here.
+// Ends with the first block after which the sum cannot become finite again, so
+// that rows of NaNs (unused ones, say) cost little.
 template <int QT>
 __device__ inline float plain_output(const MMOp &o, int64_t row, int64_t col, int b0, int b1) {
-  constexpr int QSB = (QT == EB_Q8_0) ? 32 : 16;
-  const uint16_t *x = o.x + row * o.k;
-  const uint8_t *q = o.w + col * (o.k / kQK) * QSB;
+  constexpr int C = QT == EB_Q8_0 ? 4 : 2;  // 8-byte pieces of codes per block
+  const uint4 *x = reinterpret_cast<const uint4 *>(o.x + row * o.k);
+  const uint2 *q = reinterpret_cast<const uint2 *>(o.w) + col * (o.k / kQK) * C;
   const _Float16 *d = reinterpret_cast<const _Float16 *>(o.w + o.d_off) + col * o.ds;
   float acc = 0.f;
 #pragma unroll 1
-  for (int b = b0; b < b1; ++b) {
-#pragma unroll 1
-    for (int j = 0; j < kQK; ++j) {
-      const int c = QT == EB_Q8_0 ? (int)(int8_t)q[b * 32 + j] : (q[b * 16 + (j & 15)] >> (j & 16 ? 4 : 0) & 15) - 8;
-      acc = __builtin_fmaf(__uint_as_float((uint32_t)x[b * kQK + j] << 16), (float)c * (float)d[b], acc);
+  for (int p = 4 * b0; p < 4 * b1 && __builtin_isfinite(acc); ++p) {  // 8 weights
+    const float dv = (float)d[p / 4];
+    const uint4 xv = x[p];
+    uint2 qv = q[p / 4 * C + p % C];
+    if (QT == EB_Q4_0) {
+      const int sh = p & 2 ? 4 : 0;
+      qv = make_uint2(qv.x >> sh & 0x0f0f0f0fu, qv.y >> sh & 0x0f0f0f0fu);
+    }
+    const uint32_t xs[4] = {xv.x, xv.y, xv.z, xv.w}, qs[2] = {qv.x, qv.y};
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int8_t c = (int8_t)(qs[j / 4] >> (8 * (j % 4)));
+      const float w = (float)(QT == EB_Q8_0 ? c : c - 8) * dv;
+      acc = __builtin_fmaf(__uint_as_float(j % 2 ? xs[j / 2] & 0xffff0000u : xs[j / 2] << 16), w, acc);
     }
   }
   return acc;
