@@ -449,7 +449,6 @@ eb_status build_plan(const eb_qlinear_op *ops, int32_t n_ops, uint8_t *wsbase, P
     for (MMOp &e : run) {
       s.units += rows_units(s.rt, e.m, e.n);
       e.unit_end = s.units;
-      e.tiles_n = (e.n + 16 * s.rt.nt - 1) / (16 * s.rt.nt);
     }
     s.nops = (int)run.size();
     mmhost.insert(mmhost.end(), run.begin(), run.end());

@@ -243,7 +243,7 @@ struct MMOp {
   int64_t d_off;       // scale-plane offset
   int64_t unit_end;    // workgroups of this op and all ops before it
   int32_t ds, m, n, k; // ds: scale-plane row stride (elements)
-  int32_t tiles_n, yt, pad;
+  int32_t yt, pad;
   Fuse f;
 };
 constexpr int64_t kMMaxK = int64_t(1) << 22;  // k < this keeps per-tile byte spans in 31 bits

@@ -403,12 +403,15 @@ __device__ inline void rows_unit(const MMOp &o, int nt, int mt, int sp, int spli
     put(std::integral_constant<int, EB_BF16>{});
 }
 
-// unit u of an op -> (n tile, m tile): the m tiles of an n tile 8 apart (the
-// same XCD, so its L2 serves the weights again)
-__device__ inline void unit_tile(int u, int tiles_m, int &nt, int &mt) {
-  const int g = u / (kXcds * tiles_m), r = u % (kXcds * tiles_m);
-  nt = g * kXcds + r % kXcds;
-  mt = r / kXcds;
+// Unit u of an op's tiles -> (n tile, m tile).  Units of one residue modulo 8
+// run on one XCD: it takes a stretch of the tiles in n-major order, so that its
+// L2 serves the weights of an n tile again, and the stretches differ by at most
+// one tile (whole columns per XCD left some idle: Q4_0, 925 rows of 10592 -> 237
+// took 36.8 us, the tile kernel 27.1, this order 21.5 with the tiles chosen for it).
+__device__ inline void unit_tile(uint32_t u, uint32_t tiles, uint32_t tiles_m, int &nt, int &mt) {
+  const uint32_t x = u % kXcds, t = x * (tiles / kXcds) + min(x, tiles % kXcds) + u / kXcds;
+  nt = (int)(t / tiles_m);
+  mt = (int)(t - (uint32_t)nt * tiles_m);
 }
 
 template <int QT, int XT, int NT, int MB, int W, int R>
@@ -416,8 +419,7 @@ __global__ void __launch_bounds__(W * 64)
     mm_rows_kernel(MMOp o, int tiles_m, int splits, float *__restrict__ ws, int64_t ws_stride) {
   __shared__ __attribute__((aligned(1024))) uint8_t smem[RowsTile<QT, NT, MB, W, R>::kLds];
   int nt, mt;
-  unit_tile((int)blockIdx.x, tiles_m, nt, mt);
-  if (nt >= o.tiles_n) return;
+  unit_tile(blockIdx.x, gridDim.x, tiles_m, nt, mt);
   rows_unit<QT, XT, NT, MB, W, R>(o, nt, mt, (int)blockIdx.y, splits, ws, ws_stride, smem);
 }
 
@@ -435,8 +437,7 @@ __global__ void __launch_bounds__(W * 64)
   const int64_t first = lo ? ops[lo - 1].unit_end : 0;
   const int tiles_m = (o.m + 16 * MB - 1) / (16 * MB);
   int nt, mt;
-  unit_tile((int)(u - first), tiles_m, nt, mt);
-  if (nt >= o.tiles_n) return;
+  unit_tile((uint32_t)(u - first), (uint32_t)(o.unit_end - first), tiles_m, nt, mt);
   rows_unit<QT, XT, NT, MB, W, R>(o, nt, mt, 0, 1, nullptr, 0, smem);
 }
 
@@ -444,11 +445,9 @@ __global__ void __launch_bounds__(W * 64)
 template <int QT, int XT, int NT, int MB, int W = 8>
 hipError_t launch_lone(const MMOp &op, int splits, float *ws, int64_t ws_stride, hipStream_t s) {
   constexpr int R = 3;
-  MMOp o = op;
-  o.tiles_n = (o.n + 16 * NT - 1) / (16 * NT);
-  const int tiles_m = (o.m + 16 * MB - 1) / (16 * MB);
-  const dim3 grid((unsigned)(round_up(o.tiles_n, kXcds) * tiles_m), (unsigned)splits);
-  mm_rows_kernel<QT, XT, NT, MB, W, R><<<grid, W * 64, 0, s>>>(o, tiles_m, splits, ws, ws_stride);
+  const int64_t tiles_n = (op.n + 16 * NT - 1) / (16 * NT), tiles_m = (op.m + 16 * MB - 1) / (16 * MB);
+  const dim3 grid((unsigned)(tiles_n * tiles_m), (unsigned)splits);
+  mm_rows_kernel<QT, XT, NT, MB, W, R><<<grid, W * 64, 0, s>>>(op, (int)tiles_m, splits, ws, ws_stride);
   return hipGetLastError();
 }
 

@@ -86,7 +86,7 @@ RowsTiles rows_plan(int64_t m, int64_t n, int64_t k, size_t max_ws, int cus) {
 }
 
 int64_t rows_units(const RowsTiles &t, int64_t m, int64_t n) {
-  return round_up((n + 16 * t.nt - 1) / (16 * t.nt), 8) * ((m + 16 * t.mb - 1) / (16 * t.mb));
+  return ((n + 16 * t.nt - 1) / (16 * t.nt)) * ((m + 16 * t.mb - 1) / (16 * t.mb));
 }
 
 RowsTiles rows_plan_multi(const std::vector<MMOp> &ops, int cus) {

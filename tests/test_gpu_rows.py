@@ -39,6 +39,7 @@ FORMATS = [("q8_0", torch.bfloat16), ("q8_0", torch.float16), ("q4_0", torch.bfl
     (49, 3001, 1504), (64, 4097, 256), (65, 2049, 288), (77, 3008, 96),       # one or two row tiles
     (100, 8191, 288), (128, 8193, 224), (128, 16400, 64), (31, 20000, 64),    # wide tiles of the weights
     (129, 1000, 288), (300, 1025, 96), (816, 2560, 160), (700, 4097, 32),     # more rows, tiles of four waves
+    (1100, 9, 96), (925, 237, 1056), (513, 150, 2080),                       # fewer columns of tiles than XCDs
 ])
 def test_rows_lone(eb, oracle, qtype, xdtype, m, n, k):
     w = W.normal((n, k), 7 * n + k, "cpu", W.WEIGHT_STD)
