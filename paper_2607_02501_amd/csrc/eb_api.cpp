@@ -199,6 +199,13 @@ hipError_t launch_mfma_op(const eb_qlinear_op &o, const MfmaPlan &P, void *xbuf,
                      norm_next);
 }
 
+// Whether an op is planned as one whose output the next op of a stack normalises
+// (rows_plan's norm_next).  Decided by the op alone, so that it gets the same
+// split, and bits, in a stack and by itself: residual additions end the halves
+// of a decoder layer.  Below k = 768 a split costs a lone call more than the row
+// kernel it may save (9 rows 352 -> 328: 3.8 us unsplit, 5.3 split).
+bool norm_may_follow(const eb_qlinear_op &o) { return o.epilogue == EB_EPI_ADD && o.w.k >= 768; }
+
 // Scratch of one op on the MFMA path inside a workspace of `cap` bytes: the
 // normalised activations of a prologue (xb bytes at offset 0), then the
 // split-K partial sums of the plan (P.ws_bytes, only if they fit).
@@ -212,7 +219,8 @@ OpScratch op_scratch(const eb_qlinear_op &o, size_t cap, int force_cfg = -1, int
   OpScratch r;
   r.xb = xhat_bytes(o);
   const size_t left = cap > r.xb ? std::min(cap - r.xb, kMaxSplitWorkspace) : 0;
-  r.P = plan_mfma(o.w.type, o.x_type, o.m, o.w.n, o.w.k, left, force_cfg, force_splits);
+  r.P = plan_mfma(o.w.type, o.x_type, o.m, o.w.n, o.w.k, left, force_cfg, force_splits,
+                  norm_may_follow(o));
   r.total = r.xb + r.P.ws_bytes;
   return r;
 }
@@ -648,7 +656,8 @@ eb_status build_plan(const eb_qlinear_op *ops, int32_t n_ops, uint8_t *wsbase, P
     const eb_qlinear_op &o = ops[s.op];
     if (o.m == 0 || pick_path(o.w.type, o.x_type, o.m, o.w.n, o.w.k) != EB_PATH_MFMA) continue;
     s.mfma = true;
-    s.mp = plan_mfma(o.w.type, o.x_type, o.m, o.w.n, o.w.k, kMaxSplitWorkspace);
+    s.mp = plan_mfma(o.w.type, o.x_type, o.m, o.w.n, o.w.k, kMaxSplitWorkspace, -1, 0,
+                     norm_may_follow(o));
     P.ws_bytes = std::max(P.ws_bytes, s.mp.ws_bytes);
     P.xbuf_bytes = std::max(P.xbuf_bytes, xhat_bytes(o));
   }

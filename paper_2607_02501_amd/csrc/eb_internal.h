@@ -158,9 +158,10 @@ struct MfmaPlan {
 };
 // max_ws: bytes of partial-sum workspace the call may use (0: no split);
 // force_cfg >= 0 / force_splits > 0 fix the tile configuration / split count
-// (tuning and tests; a forced choice that does not fit is not taken).
+// (tuning and tests; a forced choice that does not fit is not taken);
+// norm_next: see rows_plan.
 MfmaPlan plan_mfma(int32_t type, int32_t xt, int64_t m, int64_t n, int64_t k, size_t max_ws,
-                   int force_cfg = -1, int force_splits = 0);
+                   int force_cfg = -1, int force_splits = 0, bool norm_next = false);
 constexpr size_t kMaxSplitWorkspace = size_t(64) << 20;  // partial sums a plan may ask for
 // ws == nullptr runs the plan's configuration unsplit.  norm_next (split runs
 // with an fp32 output and no gated product only) fuses the next projection's
@@ -251,8 +252,12 @@ constexpr int64_t kRowsMaxM = 128;        // and beyond, up to
 constexpr double kRowsMaxFlops = 9e9;     // this much work
 constexpr int kRowsMaxSplits = 8;
 bool rows_fits(int64_t m, int64_t n, int64_t k);
-// Tile and split of k of a lone projection; partial sums take at most max_ws bytes.
-RowsTiles rows_plan(int64_t m, int64_t n, int64_t k, size_t max_ws, int cus);
+// Tile and split of k of a lone projection; partial sums take at most max_ws
+// bytes.  norm_next: in a stack, a reduction may also normalise the output for
+// the next op, whose own row kernel costs kNormLaunchUs.
+constexpr double kNormLaunchUs = 2.5;
+RowsTiles rows_plan(int32_t type, int64_t m, int64_t n, int64_t k, size_t max_ws, int cus,
+                    bool norm_next = false);
 RowsTiles rows_plan_multi(const std::vector<MMOp> &ops, int cus);  // of a fused run
 int64_t rows_units(const RowsTiles &t, int64_t m, int64_t n);      // its workgroups for one op
 MMOp rows_op(int32_t type, const void *w, int64_t n, int64_t k, const void *x, int64_t m, void *y,

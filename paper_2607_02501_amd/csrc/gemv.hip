@@ -1013,7 +1013,7 @@ hipError_t launch_gemv(int32_t type, const void *wdata, int64_t n, int64_t k, co
                        int32_t xt, int64_t m, void *y, int32_t yt, const Fuse &f, hipStream_t s) {
   if (type == EB_Q6_S) return launch_gemv_q6(wdata, n, k, x, xt, m, y, yt, f, s);
   if (f.pro == EB_PRO_NONE && rows_reads_faster(type, xt, m, n, k))
-    return launch_rows(type, xt, rows_plan(m, n, k, 0, device_cu_count()),
+    return launch_rows(type, xt, rows_plan(type, m, n, k, 0, device_cu_count()),
                        rows_op(type, wdata, n, k, x, m, y, yt, f), nullptr, s);
   if (type == EB_Q4_0) {
     if (xt == EB_F16) return launch_m<EB_Q4_0, EB_F16>(wdata, n, k, x, m, y, yt, f, s);

@@ -138,7 +138,7 @@ double mfma_cfg_rate(int cfg) { return kCfgs[cfg].rate; }
 bool needs_hl(int32_t xt, int64_t m) { return xt == EB_BF16 && m <= kHLMaxM; }
 
 MfmaPlan plan_mfma(int32_t type, int32_t xt, int64_t m, int64_t n, int64_t k, size_t max_ws,
-                   int force_cfg, int force_splits) {
+                   int force_cfg, int force_splits, bool norm_next) {
   const int64_t nk = (k + kBK - 1) / kBK;
   const int cus = device_cu_count();
   const bool hl = needs_hl(xt, m);
@@ -162,7 +162,7 @@ MfmaPlan plan_mfma(int32_t type, int32_t xt, int64_t m, int64_t n, int64_t k, si
   // a lone small-m projection: the small-m kernel (mfma_rows.h), measured at
   // 16 to 128 rows 1.1 to 3 times as fast as the tile kernel
   if (fc < 0 && fs <= 0 && type != EB_Q6_S && rows_fits(m, n, k)) {
-    best.rt = rows_plan(m, n, k, max_ws, cus);
+    best.rt = rows_plan(type, m, n, k, max_ws, cus, norm_next);
     best.rows = true;
     best.hl = false;
     best.splits = best.rt.splits;

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cmath>
 
 #include "eb_internal.h"
 
@@ -11,32 +12,39 @@ namespace eb {
 
 namespace {
 
-// Estimated time (us) of a lone launch: a launch and its first copies, then
-// for every round of workgroups over the CUs its steps of k (one block per
-// wave), each with a part for the rows of x, for the weight rows and for their
-// product.  Most tiles of eight waves have a CU to themselves; of those of four
-// (NT = 4) two share one, and of those of at most 16 rows and 32 weight rows
-// three or more, which then take turns at 0.85 of a round each without the last
-// one's idle CUs (Q8_0 11008 x 4096 at 2 to 16 rows: 64-row tiles of the weights
-// 14.0 to 15.2 us, 32-row ones 12.8 to 13.8).  Fitted to launches of 1024..4096 -> 1024..8192 at
-// 16 to 816 rows (Q8_0, bfloat16): within 15%, and it ranks the tiles as the
-// measurements do.
-double lone_us(const RowsTiles &t, int64_t m, int64_t n, int64_t k, int cus) {
-  const int64_t units = ((n + 16 * t.nt - 1) / (16 * t.nt)) * ((m + 16 * t.mb - 1) / (16 * t.mb)) * t.splits;
+// Workgroups of a tile that share a CU (LDS, and registers where NT = 4).
+int per_cu(const RowsTiles &t) {
+  constexpr int k8[3][4] = {{4, 2, 1, 1}, {3, 2, 1, 1}, {2, 1, 1, 1}}, k4[4] = {4, 3, 2, 2};
+  return t.w == 4 ? k4[t.mb - 1] : k8[t.nt == 1 ? 0 : t.nt == 2 ? 1 : 2][t.mb - 1];
+}
+
+// Estimated time (us) of a lone launch: the launch and its first copies, then
+// rounds of as many workgroups side by side as a CU takes.  In a round each
+// workgroup's step of k (one block per wave) keeps the CU busy for the rows of
+// x, the weight rows and their product, and waits for a while on its own; its
+// ends (adding up the waves' tiles, the outputs) pass partly beside the others'.
+// At least the time of reading x and the weights.  A split adds the reduction:
+// its launch, its chain of loads and its traffic.
+// Fitted to 56 thousand launches of 3200 problems (2 to 2500 rows, 16 to 26000
+// outputs, k of 32 to 12288, both formats and activation types): 7% rms near the
+// best tile, whose time the chosen tile's exceeds by 0.5% in the mean (up to 128
+// rows and 6000 outputs), 1.2% (more outputs) and 2.4% (more rows).
+double lone_us(const RowsTiles &t, int32_t type, int64_t m, int64_t n, int64_t k, int cus) {
   const int64_t steps = (k / kQK + t.w - 1) / t.w, per = (steps + t.splits - 1) / t.splits;
-  double us = 3.0;
-  if (t.w == 8) {
-    const double step = 0.115 + 0.05 * t.mb + 0.105 * t.nt + 0.02 * t.nt * t.mb;
-    double rounds = (double)((units + cus - 1) / cus);
-    if (t.mb == 1 && t.nt <= 2) rounds = std::max(1.0, 0.85 * (double)units / cus);
-    us += rounds * (double)per * step;
-  } else {
-    const int64_t rounds = (units + 2 * cus - 1) / (2 * cus);
-    const double step = (0.3 + 0.17 * t.mb) * (units <= cus ? 0.7 : 1.0);
-    us += (rounds > 1 ? 0.85 : 1.0) * (double)rounds * (double)per * step;
-  }
-  // the reduction of the partial sums: a launch, and their traffic
-  if (t.splits > 1) us += 3.2 + (double)(t.splits + 1) * (double)m * (double)n * 4 / 4e6;
+  const double busy = t.w == 8 ? 0.076 * t.mb + 0.08 * t.nt + 0.021 * t.nt * t.mb : 0.22 + 0.056 * t.mb;
+  const double step = busy + (t.w == 8 ? 0.065 : 0.125);
+  const double ends = (t.w == 8 ? 1.1 : 0.22) + 0.057 * t.nt * t.mb * 8 / t.w;
+  auto round = [&](double c) {  // of c workgroups per CU; c < 1: on a part of the CUs
+    return ends * (1 + 0.33 * (c - 1)) + (double)per * std::max(step, std::ceil(c) * busy);
+  };
+  const int occ = per_cu(t);
+  const double units = (double)(rows_units(t, m, n) * t.splits) / cus, full = std::floor(units / occ);
+  const double rest = units - full * occ;
+  double us = full * round(occ);
+  if (rest > 0) us += round(rest < 1 ? rest : std::ceil(rest));
+  const double bytes = 2.0 * m * k + (double)n * k * (type == EB_Q8_0 ? 34 : 18) / 32;
+  us = 2.7 + std::max(us, bytes / 3.85e6);
+  if (t.splits > 1) us += 1.7 + 0.15 * t.splits + (t.splits + 1.0) * m * n * 4 / 2.86e6;
   return us;
 }
 
@@ -47,19 +55,25 @@ bool rows_fits(int64_t m, int64_t n, int64_t k) {
   // more work to reach it (measured, Q8_0, us, this kernel against it: 160
   // rows 2048 -> 2560 9 against 18, 300 rows 1024 -> 1024 6 against 13, 816
   // rows 2048 -> 2560, 8.6 GFLOP, 25 against 30; 2000 rows 2976 -> 1000, 11.9
-  // GFLOP, 32 against 30).  Offsets inside a tile's rows of x, weights and y stay below
-  // 2^31 (an offset of 2^31 or more reads zero and stores nothing).
+  // GFLOP, 32 against 30; 990 problems of 129 to 2500 rows up to 9 GFLOP 0.64
+  // times as long in the mean).  Behind it are short k with outputs of 6 MB and
+  // more, where a workgroup's ends count (2408 rows 64 -> 5685 29 against 22):
+  // they stay here for the exact weights.  Offsets inside a tile's rows of x,
+  // weights and y stay below 2^31 (an offset of 2^31 or more reads zero and
+  // stores nothing).
   return m >= 1 && (m <= kRowsMaxM || 2.0 * (double)m * (double)n * (double)k <= kRowsMaxFlops) &&
          64 * k * 2 < 0x7fff0000LL && 64 * n * 4 < 0x7fff0000LL;
 }
 
-RowsTiles rows_plan(int64_t m, int64_t n, int64_t k, size_t max_ws, int cus) {
-  // When the 16-row tiles of the weights leave two thirds of the CUs idle, k
-  // is split whatever the estimate says: in a layer chain the reduction then
-  // also normalises for the next projection, a launch that would follow anyway.
-  const int64_t wgs = (n + 15) / 16, steps = (k / kQK + 7) / 8;
+RowsTiles rows_plan(int32_t type, int64_t m, int64_t n, int64_t k, size_t max_ws, int cus, bool norm_next) {
+  const int64_t steps = (k / kQK + 7) / 8;
   const int most = (int)std::max<int64_t>(1, std::min<int64_t>(kRowsMaxSplits, steps));
-  const bool split = m <= kRowsMaxM && cus / wgs >= 3 && most > 1;
+  // Few columns (16-row tiles of the weights for a third of the CUs at most): from
+  // k = 4096 on a split takes less than the estimate says (0.75 times as long as
+  // unsplit in the mean of 123 problems of 2 to 128 rows; equal at 2048 to 4095,
+  // 1.2 to 1.4 times below), and a reduction may save the row kernel.
+  const bool few = m <= kRowsMaxM && cus / ((n + 15) / 16) >= 3;
+  const double unsplit_us = few && (norm_next || k >= 4096) ? kNormLaunchUs : 0.0;
   RowsTiles best;
   double best_t = 0;
   for (int sp = 1; sp <= most; ++sp) {
@@ -75,8 +89,8 @@ RowsTiles rows_plan(int64_t m, int64_t n, int64_t k, size_t max_ws, int cus) {
         t.w = c < 3 ? 8 : 4;
         t.splits = sp;
         t.ws_stride = sp > 1 ? stride : 0;
-        const double us = lone_us(t, m, n, k, cus);
-        if (best.nt == 0 || (split && best.splits == 1 && sp > 1) || us < best_t) {
+        const double us = lone_us(t, type, m, n, k, cus) + (sp == 1 ? unsplit_us : 0.0);
+        if (best.nt == 0 || us < best_t) {
           best_t = us;
           best = t;
         }

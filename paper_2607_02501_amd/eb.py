@@ -254,8 +254,8 @@ def _run_tuned(op: eb_qlinear_op, device, tile: int, splits: int) -> None:
 # One projection called directly: at one token the kernel takes about 4 us, so
 # the call's host time counts.  The op is packed into bytes of eb_qlinear_op's
 # layout (0.2 us; building the two nested structures takes 1.1), and the size
-# of its workspace, which depends on the shape, types, path and device alone, is
-# asked for once and kept after a call that succeeded.  Measured at m = 1,
+# of its workspace, which depends on the shape, types, steps, path and device alone,
+# is asked for once and kept after a call that succeeded.  Measured at m = 1,
 # 2048 -> 2048 (kernel 4 us): 10.1 us per call before, 7.2 now.
 _PACK_OP = struct.Struct("iiqqPPPqiiiiPPfi")
 assert _PACK_OP.size == ctypes.sizeof(eb_qlinear_op)
@@ -277,7 +277,7 @@ def _run_op(qw: QWeights, x: torch.Tensor, out: torch.Tensor, x_type: int, path:
                        x_type, DTYPES[out.dtype], prologue, epilogue,
                        norm_weight.data_ptr() if norm_weight is not None else 0,
                        residual.data_ptr() if residual is not None else 0, eps, 0)
-    key = (qtype, m, qw.n, qw.k, x_type, prologue, path, dev)
+    key = (qtype, m, qw.n, qw.k, x_type, prologue, epilogue, path, dev)
     nbytes = _WS_BYTES.get(key)
     known = nbytes is not None
     if not known:

@@ -548,6 +548,17 @@ def test_workspace_sizes(eb):
     assert eb.lib.eb_qlinear_stack_workspace_bytes(arr, 0) == 0
 
 
+@pytest.mark.parametrize("m,n,k,split", [
+    (9, 328, 352, 0), (50, 1024, 1024, 0), (77, 1360, 1024, 0), (100, 1000, 512, 0), (128, 1024, 1024, 0),
+    (50, 1024, 4096, 1), (100, 1024, 4096, 1), (4, 512, 8192, 1)])
+def test_lone_small_m_split_follows_the_estimate(eb, m, n, k, split):
+    """k is split only where the shorter steps save more than the reduction
+    costs (these unsplit ones measured 3.7 to 5 us, split 5 to 7.6)."""
+    op = eb.eb_qlinear_op(_w(eb, eb.EB_Q8_0, n=n, k=k, data=1 * GB), 8 * GB, 9 * GB, m, eb.EB_BF16,
+                          eb.EB_F32)
+    assert (eb.lib.eb_qlinear_workspace_bytes(ctypes.byref(op), eb.EB_PATH_MFMA) > 0) == bool(split)
+
+
 def test_workspace_validation(eb):
     """A workspace must be 256-byte aligned, overlap no operand, and be given
     whenever its size is; a prologue on the MFMA path needs one."""
