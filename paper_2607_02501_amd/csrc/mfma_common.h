@@ -15,7 +15,6 @@ typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef _Float16 f16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
 
 constexpr int kBK = 64;        // K elements per tile (2 blocks)
 constexpr int kXcds = 8;
@@ -212,18 +211,6 @@ __device__ inline __amdgpu_buffer_rsrc_t rsrc(const void *base, uint32_t bytes) 
                                            0x00020000);
 }
 
-// The same for a base and size that are uniform across the wave but that the
-// compiler cannot prove uniform (cursor state carried through loops): without
-// the read-first-lane it keeps them in vector registers and wraps every load
-// in a loop over distinct descriptor values.
-__device__ inline __amdgpu_buffer_rsrc_t ursrc(const void *base, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(base);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
-  return rsrc(reinterpret_cast<const void *>(((uint64_t)hi << 32) | lo),
-              __builtin_amdgcn_readfirstlane(bytes));
-}
-
 __device__ inline uint4 bload(__amdgpu_buffer_rsrc_t r, uint32_t voff) {
   const auto v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, 0, 0);
   return make_uint4(v[0], v[1], v[2], v[3]);
@@ -280,7 +267,7 @@ __device__ inline void advance(i32x4_t &r, uint32_t by) {
 // ones into other stages too; the step's own wait and barrier order them.
 __device__ inline void copy_lds(i32x4_t r, uint32_t voff, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"(r) : "memory");
+               ::"s"(__builtin_amdgcn_readfirstlane(lds)), "v"(voff), "s"(r) : "memory", "m0");
 }
 
 }  // namespace
