@@ -341,7 +341,7 @@ struct Step {
   bool mfma = false;  // single op on the MFMA path, run with plan `mp`
   MfmaPlan mp;
   bool mm = false;    // fused MFMA launch (op == -1)
-  int32_t type = 0, xt = 0, yt = 0;
+  int32_t type = 0, xt = 0;
   int ns = 0;
   size_t table = 0;   // first entry in the device table (M1Op or MMOp)
   int nops = 0;
