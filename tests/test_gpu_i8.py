@@ -60,7 +60,7 @@ def _x8_reference(oracle, qtype, w_rows, x, rows=None):
 @pytest.mark.parametrize("qtype", ["q8_0", "q4_0"])
 @pytest.mark.parametrize("xdtype", [torch.float16, torch.bfloat16])
 def test_i8_codes_bit_exact_and_parity(eb, oracle, qtype, xdtype):
-    """Ragged m and n around the 128 x 128 tiles, 65 blocks of k."""
+    """Ragged m and n around the 64 x 64 tiles that few tiles take, 65 blocks of k."""
     n, k = 300, 2080
     w = W.normal((n, k), 1500, "cpu", W.WEIGHT_STD)
     qw = eb.quantize(w.to(DEV), qtype)
@@ -100,6 +100,36 @@ def test_i8_epilogues(eb, oracle, qtype):
     silu = oracle.silu_mul(g, np.ones_like(g))
     scale = 1.1 * b8[:, 0::2] * np.abs(u) + np.abs(silu) * b8[:, 1::2] + 0.0022 * b8[:, 0::2] * b8[:, 1::2]
     assert_parity(y, ref, scale, TOL_F32, "i8_glu")
+
+
+@pytest.mark.parametrize("qtype", ["q8_0", "q4_0"])
+@pytest.mark.parametrize("k", [32, 160, 256])
+def test_i8_large_tiles(eb, oracle, qtype, k):
+    """The 128 x 128 tiles, taken from two per CU on: n of two tiles and a
+    remainder, a remainder of rows, k of one block, of a whole and a part of a
+    step of four, and of whole steps; each epilogue, fp32 and 16-bit outputs.
+    The rows of the first, an inner and the last row tile are compared."""
+    n = 2 * 128 + 44
+    row_tiles = -(-2 * torch.cuda.get_device_properties(0).multi_processor_count // 3)
+    m = 128 * row_tiles - 35
+    w = W.normal((n, k), 1650 + k, "cpu", W.WEIGHT_STD)
+    qw = eb.quantize(w.to(DEV), qtype)
+    x = W.normal((m, k), 1651 + k, "cpu").to(torch.bfloat16)
+    rows = np.r_[0:130, 128 * 9 - 2:128 * 9 + 3, m - 95:m]
+    y8, b8, _, _, _, _, _ = _x8_reference(oracle, qtype, w.numpy(), x, torch.from_numpy(rows))
+    xd, rd = x.to(DEV), torch.from_numpy(rows).to(DEV)
+    y, _ = _run_i8(eb, qw, xd)
+    assert_parity(y[rd], y8, b8, TOL_F32, f"i8_large {qtype} k={k}")
+    y, _ = _run_i8(eb, qw, xd, out_dtype=torch.bfloat16)
+    assert_parity(y[rd], y8, b8, TOL_BF16, f"i8_large {qtype} k={k}")
+    r = W.normal((m, n), 1652 + k, "cpu")
+    y, _ = _run_i8(eb, qw, xd, epilogue="add", residual=r.to(DEV))
+    assert_parity(y[rd], y8 + r[rows].double().numpy(), b8, TOL_F32, f"i8_large_add {qtype} k={k}")
+    y, _ = _run_i8(eb, qw, xd, epilogue="glu")
+    g, u = y8[:, 0::2], y8[:, 1::2]
+    silu = oracle.silu_mul(g, np.ones_like(g))
+    scale = 1.1 * b8[:, 0::2] * np.abs(u) + np.abs(silu) * b8[:, 1::2] + 0.0022 * b8[:, 0::2] * b8[:, 1::2]
+    assert_parity(y[rd], oracle.silu_mul(g, u), scale, TOL_F32, f"i8_large_glu {qtype} k={k}")
 
 
 @pytest.mark.parametrize("kind", ["onehot", "outlier", "sparse"])
