@@ -130,11 +130,10 @@ def test_qlinear_mfma_parity(eb, oracle, qtype, xdtype, n, k):
 
 @pytest.mark.parametrize("qtype,xdtype", [("q8_0", torch.bfloat16), ("q4_0", torch.float16)])
 def test_narrow_kernel_edges(eb, oracle, qtype, xdtype):
-    """Lone small-m MFMA projections at the edges of the narrow kernel: every
-    count of 16-row blocks of m (1, 2, 4) and the m just past each, a ragged
-    last group of 16 weight rows, k at its limit (2048 = 64 blocks over 8
-    waves) and one block past it (the tiled kernel with a split of k), and an
-    uneven share of k between the waves (k = 11 blocks)."""
+    """Lone projections of few rows on the MFMA path: every count of 16-row
+    blocks of a tile (1 to 4) and the m just past each, a ragged last group of
+    weight rows, and k of one step of eight blocks and a part of one (11
+    blocks), of whole steps (64) and of one block more (65)."""
     n = 1000 + 3
     for k in (352, 2048, 2080):
         w, x = _case(3000 + k, n, k, 64, xdtype)
@@ -310,8 +309,7 @@ def test_fused_decode_stack_matches_single_calls(eb, qtype, xdtype, monkeypatch)
     ("q8_0", torch.float16, torch.bfloat16, (64, 7, 128, 65)),
 ])
 def test_fused_mfma_stack(eb, oracle, qtype, xdtype, ydtype, ms, monkeypatch):
-    """Independent small-m MFMA ops run as one persistent launch (weights
-    dequantized into MFMA registers): every output within the oracle bound,
+    """Independent small-m MFMA ops run as one launch over their tiles: every output within the oracle bound,
     the same bits on every run and in every stack mode, and the single-call
     results up to summation order."""
     monkeypatch.delenv("EB_STACK_FUSE", raising=False)
