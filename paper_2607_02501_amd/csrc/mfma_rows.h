@@ -336,20 +336,32 @@ __device__ inline void rows_unit(const MMOp &o, int nt, int mt, int sp, int spli
 #pragma unroll
       for (int i = 0; i < 4; ++i) v[u][i] += a[i];
     }
-    if constexpr (XT == EB_BF16) {
-      const int l = e & 63, tile = e >> 6;
-      const int cl = 16 * (tile / MB) + (l & 15), rl = 16 * (tile % MB) + 4 * (l >> 4);
+  }
+  if constexpr (XT == EB_BF16) {
+    // sums that are not finite (0 times one is no number), all at once: a branch
+    // per float4 would have every LDS read above wait for the one before
+    float z = 0.f;
+#pragma unroll
+    for (int u = 0; u < EPT; ++u)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) z = __builtin_fmaf(v[u][i], 0.f, z);
+    if (__builtin_expect(z != 0.f, 0)) {
       uint32_t lost = 0;
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-        if (!__builtin_isfinite(v[u][i]) && rl + i < rows_m && cl < rows_n) lost |= 1u << i;
+      for (int u = 0; u < EPT; ++u)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) lost |= __builtin_isfinite(v[u][i]) ? 0u : 1u << (4 * u + i);
 #pragma unroll 1
       for (; lost; lost &= lost - 1) {
-        const int j = __builtin_ctz(lost);
-        const float r = plain_output<QT>(o, m0 + rl + j, n0 + cl, s0 * W, min(nb, s1 * W));
+        const int j = __builtin_ctz(lost), e = t + (j >> 2) * W * 64, l = e & 63, tile = e >> 6;
+        const int cl = 16 * (tile / MB) + (l & 15), rl = 16 * (tile % MB) + 4 * (l >> 4) + (j & 3);
+        if (rl >= rows_m || cl >= rows_n) continue;
+        const float r = plain_output<QT>(o, m0 + rl, n0 + cl, s0 * W, min(nb, s1 * W));
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (i == j) v[u][i] = r;
+        for (int u = 0; u < EPT; ++u)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            if (4 * u + i == j) v[u][i] = r;
       }
     }
   }
