@@ -108,7 +108,7 @@ typedef int32_t eb_status;
 /* kernel paths for eb_qlinear_ex */
 #define EB_PATH_AUTO 0 /* pick by m, qtype and shape (measured crossover) */
 #define EB_PATH_GEMV 1 /* bandwidth-bound, no workspace, requires m <= 8 and m' * k <= 65536, m' = m rounded up to 1, 2, 4 or 8 */
-#define EB_PATH_MFMA 2 /* LDS-tiled dequantize-to-16-bit + MFMA, any m */
+#define EB_PATH_MFMA 2 /* LDS-tiled MFMA, any m: on the integer codes (few rows or little work) or on weights dequantized to 16 bits */
 /* Low-precision prefill variant (section 3.2, backend-specific dispatch), Q8_0 /
  * Q4_0, opt-in only (EB_PATH_AUTO never takes it): x is quantized per
  * 32-element block along k to int8 (s = fl32(max|x| / 127), codes rounded half
@@ -124,7 +124,7 @@ typedef int32_t eb_status;
  * `data` is a device pointer, 256-byte aligned, eb_qweights_bytes(type, n, k)
  * bytes; it is owned by the caller. */
 typedef struct {
-  int32_t type; /* EB_Q8_0 or EB_Q4_0 */
+  int32_t type; /* EB_Q8_0, EB_Q4_0 or EB_Q6_S */
   int32_t reserved; /* must be 0 */
   int64_t n;    /* output features (rows of W) */
   int64_t k;    /* input features (columns of W), multiple of 32 */
@@ -259,14 +259,21 @@ eb_status eb_qlinear_fused_static(const eb_qlinear_op *op, int32_t path, hipStre
  * No bias.  Accuracy, with B = sum_k |x||w_hat| per output (plus the output
  * rounding when y_type is 16-bit):
  *   - GEMV path (m <= 8), any x_type: |y - y_exact| <= 2e-3 B;
- *   - MFMA path, EB_BF16 x, m <= 128: the codes enter the matrix cores as exact
- *     integers, scaled per block in fp32 (Q6_S, and tiles forced by
- *     eb_qlinear_tuned: w_hat as hi + lo, within 2^-16): <= 2e-3 B;
- *   - MFMA path, EB_BF16 x, m > 128 (matrix-core bound): w_hat is rounded once
- *     to bfloat16 (8 significant bits): <= (2e-3 + 2^-8) B;
- *   - MFMA path, EB_F16 x: w_hat is rounded once to binary16 (11 significant
- *     bits, subnormal below 2^-14): <= 2e-3 B + 2^-25 sum_k |x|; requires
- *     |w_hat| <= 65504, i.e. max |w| <= 65504 in every block.
+ *   - MFMA path, Q8_0 and Q4_0, m <= 128, or single ops of more rows with 2 m n
+ *     k <= 9e9: the codes enter the matrix cores as exact integers, scaled per
+ *     block in fp32 (tiles forced by eb_qlinear_tuned instead take w_hat as the
+ *     next lines say): <= 2e-3 B;
+ *   - MFMA path, EB_BF16 x, m <= 128 otherwise: w_hat as hi + lo bfloat16
+ *     values, within 2^-16: <= 2e-3 B;
+ *   - MFMA path, EB_BF16 x, m > 128 otherwise (matrix-core bound): w_hat is
+ *     rounded once to bfloat16 (8 significant bits): <= (2e-3 + 2^-8) B; a
+ *     grouped stack launch may do so for ops within the first line too;
+ *   - MFMA path, EB_F16 x otherwise: w_hat is rounded once to binary16 (11
+ *     significant bits, subnormal below 2^-14): <= 2e-3 B + 2^-25 sum_k |x|;
+ *     requires |w_hat| <= 65504, i.e. max |w| <= 65504 in every block.
+ *   EB_BF16 x is taken over the whole finite range by the MFMA path; the GEMV
+ *   path's own kernels (one row, and several where they run) add up x times
+ *   codes before the scale comes in (|x| <= 7e34).
  *   (paper section 4, Table 3: the 8-/4-bit configurations are judged by the
  *   outputs they give; these bounds are this library's contract for them.)
  * EB_ERR_INVALID: w or its data NULL, bad type/sizes, an unknown x_type or

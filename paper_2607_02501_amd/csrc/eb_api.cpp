@@ -152,12 +152,17 @@ eb_status check_op(const eb_qlinear_op &o, int32_t path) {
   return EB_OK;
 }
 
-// Path choice from the measured GEMV / MFMA crossover on MI355X (single ops
-// without a workspace, replayed from a graph; Q4_0 and Q8_0 at the decode /
-// prefill / action-expert shapes): the GEMV wins at m = 1 everywhere; at
-// m = 2..4 when the matrix has 4096 rows or more (with 1024 or 2048 the
-// matrix cores win by 20-55%); at m = 5..8 where, in addition, k > 2048 (up
-// to there the small-m matrix-core kernel wins by 15-50%).
+// Path choice between the bandwidth path, which takes no workspace, and the
+// matrix-core path (measured on single ops replayed from a graph, Q4_0 and Q8_0
+// at the decode / prefill / action-expert shapes): the GEMV wins at m = 1
+// everywhere (Q4_0 4096 -> 4096 4.1 against 7.2 us).  From 2 rows on plain ops
+// mostly run the small-m kernel on either path (rows_reads_faster), in the same
+// time but where a workspace lets the matrix-core path split k (4 rows 11008 ->
+// 4096 12.7 against 17.3).  The lines n >= 4096 and k > 2048 are gemv_kernel's,
+// which normalised ops of several rows still run here: no longer the faster way
+// for a call with a workspace (Q4_0 4096 -> 12288, 2 rows 18 against 16 us, 8
+// rows 62 against 15; Q8_0 22 against 20 and 75 against 21), the only one
+// without, since the matrix-core path needs room for the normalised rows.
 // Q6_S: its GEMV up to m = 4, its matrix-core kernel beyond.
 int32_t pick_path(int32_t type, int32_t xt, int64_t m, int64_t n, int64_t k) {
   (void)xt;

@@ -22,11 +22,12 @@
 // 3 per 2 codes) and the copies, both near half busy.  x, codes and scales are copied to
 // LDS in 1 KiB pieces of whole 128- to 512-byte row segments (R - 1 steps
 // ahead): read by each wave in operand order instead, 16 rows a power of two
-// apart per load, the same loads took 2-3 times as long.  Measured, graph of
-// dependent launches, Q8_0, bfloat16 x, 50 rows: 1024 -> 2048 8.5 -> 4.4 us,
-// 1024 -> 8192 gated 14.6 -> 6.3, 4096 -> 1024 split 12.0 -> about 8 with its
-// reduction; 77 rows 1504 -> 3008 19.4 -> 6.5; 128 rows 4096 -> 8192 35 -> 20;
-// 128 fused projections of 32 action-expert layers 281 -> 187 us.
+// apart per load, the same loads took 2-3 times as long.  Measured against the
+// kernels that did so, graph of launches on distinct weights, Q8_0, bfloat16 x,
+// 50 rows: 1024 -> 2048 8.5 -> 4.7 us, 1024 -> 8192 gated 14.6 -> 6.6, 4096 ->
+// 1024 split 12.0 -> 8.8 with its reduction; 77 rows 1504 -> 3008 19.4 -> 6.8;
+// 128 rows 4096 -> 8192 35 -> 25; 128 fused projections of 32 action-expert
+// layers 281 -> 180 us.
 #ifndef EB_MFMA_ROWS_H
 #define EB_MFMA_ROWS_H
 

@@ -59,7 +59,7 @@ bool rows_fits(int64_t m, int64_t n, int64_t k) {
   // rows 2048 -> 2560, 8.6 GFLOP, 25 against 30; 2000 rows 2976 -> 1000, 11.9
   // GFLOP, 32 against 30; 990 problems of 129 to 2500 rows up to 9 GFLOP 0.64
   // times as long in the mean).  Behind it are short k with outputs of 6 MB and
-  // more, where a workgroup's ends count (2408 rows 64 -> 5685 29 against 22):
+  // more, where a workgroup's ends count (2408 rows 64 -> 5685 27 against 22):
   // they stay here for the exact weights.  Offsets inside a tile's rows of x,
   // weights and y stay below 2^31 (an offset of 2^31 or more reads zero and
   // stores nothing).
