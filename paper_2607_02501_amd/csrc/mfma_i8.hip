@@ -23,9 +23,10 @@
 // weight s_ib d_nb: fma(float(P), s_ib d_nb, acc) -- three vector ALU
 // operations per output element and block, which bound this kernel: 192 cycles
 // per 32 x 32 x 32 product, about 770 TOP/s at the clock it runs at.
-// Measured (Q8_0, 816 rows): 2048 -> 32768 269 -> 201 us (545 TOP/s), 16384 ->
-// 2048 383 -> 144 us, with operands read from memory by each wave before,
-// 32 rows a power of two apart per load, and 128 x 128 tiles only.
+// Measured, a whole call with its activation step (Q8_0, 816 bf16 rows and
+// outputs): 2048 -> 32768 289 -> 222 us (493 TOP/s; the product alone 213 us),
+// 16384 -> 2048 378 -> 137 us, with operands read from memory by each wave
+// before, 32 rows a power of two apart per load, and 128 x 128 tiles only.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -64,7 +65,7 @@ __device__ inline float code_x8(float v, float s, float r) {
 
 // Four lanes per row and block, 16 blocks of a row per wave: a wave reads 1 KiB
 // and writes 512 bytes of codes, side by side (a thread per block, 64 bytes
-// apart, and binary64 quotients took 19 us for 816 x 16384, now 13.5).
+// apart, and binary64 quotients took 19 us for 816 x 16384, now 12.5).
 template <int XT>
 __global__ void __launch_bounds__(256)
     quantize_x8_kernel(const uint16_t *__restrict__ x, int64_t m, int64_t k, int64_t ms,
@@ -329,8 +330,8 @@ hipError_t launch_mfma_i8(int32_t type, const void *wdata, int64_t n, int64_t k,
   const Layout L = layout_of(type, n, k);
   const auto *wp = static_cast<const uint8_t *>(wdata);
   // 128 x 128 tiles where they give every CU its two workgroups, else 64 x 64
-  // (measured, Q8_0, 816 rows: 16384 -> 2048, 112 large tiles, 314 us against
-  // 144; 2560 -> 2048, 140 of them, 54 us against 33)
+  // (measured, a whole call, Q8_0, 816 rows: 16384 -> 2048, 112 large tiles,
+  // 306 us against 137; 2048 -> 2560, 140 of them, 50 us against 30)
   auto launch = [&](auto fc) {
     constexpr int F = decltype(fc)::value;
     const int64_t tiles = round_up((n + 64 * F - 1) / (64 * F), kXcds) * ((m + 64 * F - 1) / (64 * F));
